@@ -49,7 +49,7 @@ TRAFFIC_BYTES = {"row_pass": 563499446, "col_pass": 521796428, "contract": 93755
 # Sources that decide the profiled kernels and their launch shapes (the
 # serving layer and the binding do not).
 KERNEL_SOURCES = ("slice_kernels.hip", "probe_kernels.hip", "probe16_kernels.hip", "fft_lds.hpp",
-                  "fft_reg.hpp", "kernels.hpp", "plan.cpp")
+                  "fft_reg.hpp", "fft_steps.hpp", "kernels.hpp", "plan.cpp")
 
 
 _TOKENS = re.compile(r'("(?:\\.|[^"\\\n])*"|\'(?:\\.|[^\'\\\n])*\')|//[^\n]*|/\*.*?\*/', re.S)
@@ -120,14 +120,13 @@ def kernel_work(name, g):
     N, H, B, P, W, BA = g["N"], g["H"], g["B"], g["P"], g["W"], g["BA"]
     state = 4.0 * N * N           # compact wave: N x N/2 complex64
     if name == "row_pass":
-        # read + write the wave state, plus the slice's transmission once per launch
-        return "hbm", B * H * 2 * state + g["launches"] * 8.0 * N * N
+        # read + write the wave state (the first slice only writes it: its plane waves
+        # are formed in the kernel), plus the slice's transmission once per launch
+        return "hbm", B * (2 * H - 1) * state + g["launches"] * 8.0 * N * N
     if name == "col_pass":
         return "hbm", B * H * 2 * state
     if name == "extract":
         return "hbm", B * (state / 2 + 2.0 * N * N)
-    if name == "beam_init":
-        return "hbm", B * state
     if name in ("contract", "contract16"):
         return "mfma", 8.0 * BA * W * W * P
     if name in ("s32_pack", "s16_pack"):

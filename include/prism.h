@@ -488,9 +488,9 @@ int prism_server_call_stats(const prism_server* server, long long* probe_calls,
  * workgroups and launches changes), chosen per grid by a tuning sweep on
  * the target GPU. A zero field means the library default (shown).
  *   row_iters, col_iters: most row groups / column tiles one workgroup of
- *     the four-step slice passes walks (powers of two up to 64; 16, 8);
+ *     the slice passes walks (powers of two up to 64; 16, 8);
  *   row_min_groups, col_min_groups: fewest workgroups a slice-pass launch
- *     keeps when choosing those counts (512, 256);
+ *     has where there is that much work (512, 256);
  *   wave_chunk_mib: wave state per slice-pass launch, which sets the
  *     preferred build and multislice workspaces (16 .. 65536; 256);
  *   probe_group: probes per window-sum group (16, 32, 64; 0: 64 for

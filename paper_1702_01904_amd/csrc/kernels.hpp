@@ -53,7 +53,7 @@ struct ProbeOptics {
 };
 
 // Launch shapes that do not change any result (work distribution only):
-// the four-step slice passes' iteration caps and smallest grids, and the
+// the slice passes' iteration caps and smallest grids, and the
 // window sum's workgroups per probe group (union tiles of one window /
 // window_tile_div). Set per plan (prism_set_tuning); defaults below.
 struct LaunchTuning {
@@ -71,24 +71,30 @@ hipError_t launch_transmission(const float* phase, float2* trans, size_t count, 
 hipError_t launch_prop_lut(float2* lut, int n, int H, const double* thick_dev, double lam,
                            double dq, hipStream_t st);
 
-hipError_t launch_beam_init(float2* state, const int32_t* beams_mn, int b0, int nb, int n, int f,
-                            const float2* twN, hipStream_t st);
+// Plane waves of a build's first slice: wave w is beam b0 + w of the (m, n)
+// list mn at interpolation factor f.
+struct BeamWaves {
+  const int32_t* mn;
+  int b0, f;
+};
 // aper[ky + n/2] = (kx_lo, kx_hi): the aperture's full-grid pixels of row ky
 // (empty when kx_lo > kx_hi), decided on the host.
 hipError_t launch_probe_init(float2* state, const double* probe_xy, int p0, int np, int n,
                              const ProbeOptics& po, const int2* aper, const float2* twN,
                              hipStream_t st);
-// Four-step slice passes (n = R^2): R, or 0 where the Stockham kernels run.
+// Four-step slice passes (n = R^2): R, or 0 where k_row_steps / k_col_steps run.
 int four_step_radix(int n);
 // tw2[m][j] = exp(-2 pi i j m / n), j, m < R (n entries; nothing for R = 0).
 hipError_t launch_twiddles2(float2* tw2, int n, hipStream_t st);
+// init != nullptr: first slice of a build, the state is only written (its
+// inputs are the beams' plane waves).
 // wtrans != nullptr: wave w multiplies by wtrans[w] + soff instead of trans_p
 // (device table of per-wave transmission bases: waves of several specimens
-// in one launch).
+// in one launch); not together with init.
 hipError_t launch_row_pass(float2* state, int nwaves, int n, const float2* trans_p,
                            const float2* twN, const float2* tw2, const LaunchTuning& tune,
-                           hipStream_t st, const float2* const* wtrans = nullptr,
-                           size_t soff = 0);
+                           hipStream_t st, const BeamWaves* init = nullptr,
+                           const float2* const* wtrans = nullptr, size_t soff = 0);
 hipError_t launch_col_pass(float2* state, int nwaves, int n, const float2* prop_p,
                            const float2* twN, const float2* tw2, const LaunchTuning& tune,
                            hipStream_t st);

@@ -1203,7 +1203,8 @@ int prism_build_smatrix(prism_plan* p, int f, double amax_mrad, void* S, size_t 
   // every launch fills the GPU and kernel timings stay exclusive.
   const int lanes =
       (PRISM_BUILD_STREAMS > 1 && chunk >= 2 && B > chunk / 2 && B <= 2 * chunk) ? 2 : 1;
-  const int sub = chunk / lanes;
+  // one chunk: its two halves (the state holds B waves); two: half a chunk each
+  const int sub = lanes == 1 ? chunk : (B <= chunk ? (B + 1) / 2 : chunk / 2);
   hipStream_t ls[2] = {st, st};
   if (lanes == 2) {
     if (!p->aux) HIP_TRY(hipStreamCreateWithFlags(&p->aux, hipStreamNonBlocking), "create build stream");
@@ -1218,9 +1219,11 @@ int prism_build_smatrix(prism_plan* p, int f, double amax_mrad, void* S, size_t 
     const int nb = std::min(sub, B - b0);
     hipStream_t sg = ls[g % lanes];
     float2* state = w.state + (size_t)(g % lanes) * sub * n * (n / 2);
-    LAUNCH(p, sg, "beam_init", prism::launch_beam_init(state, w.mn, b0, nb, n, f, w.twN, sg));
+    const prism::BeamWaves init{w.mn, b0, f};  // the first row pass forms the plane waves
     for (int s = 0; s < p->H; ++s) {
-      LAUNCH(p, sg, "row_pass", prism::launch_row_pass(state, nb, n, w.trans + (size_t)s * n * n, w.twN, w.tw2, p->tune, sg));
+      LAUNCH(p, sg, "row_pass",
+             prism::launch_row_pass(state, nb, n, w.trans + (size_t)s * n * n, w.twN, w.tw2,
+                                    p->tune, sg, s == 0 ? &init : nullptr));
       LAUNCH(p, sg, "col_pass", prism::launch_col_pass(state, nb, n, w.prop + (size_t)s * n, w.twN, w.tw2, p->tune, sg));
     }
     LAUNCH(p, sg, "extract", prism::launch_extract(state, nb, n, Sout + (size_t)b0 * splane, w.twH, sg));
@@ -1539,11 +1542,11 @@ int batch_build_group(const prism_build_item* items, const BatchGroup& g, void* 
     HIP_TRY(hipMemcpyAsync(w.wtab, kept.data(), kept.size() * sizeof(uint64_t),
                            hipMemcpyHostToDevice, st),
             "copy wave table");
-    for (const Part& pt : parts) {
-      const prism_build_item& it = items[pt.s->item];
-      LAUNCH(p, st, "beam_init",
-             prism::launch_beam_init(w.state + (size_t)pt.w0 * wave, pt.s->mn, pt.b0, pt.nb, n,
-                                     it.f, w.twN, st));
+    for (const Part& pt : parts) {  // first slice: each part forms its own plane waves
+      const prism::BeamWaves init{pt.s->mn, pt.b0, items[pt.s->item].f};
+      LAUNCH(p, st, "row_pass",
+             prism::launch_row_pass(w.state + (size_t)pt.w0 * wave, pt.nb, n, pt.s->trans, w.twN,
+                                    w.tw2, p->tune, st, &init));
     }
     // parts are in decreasing slice count: the first `active` waves still run
     const int hmax = parts.front().s->H;
@@ -1551,9 +1554,10 @@ int batch_build_group(const prism_build_item* items, const BatchGroup& g, void* 
       int active = 0;
       for (const Part& pt : parts)
         if (pt.s->H > s) active = pt.w0 + pt.nb;
-      LAUNCH(p, st, "row_pass",
-             prism::launch_row_pass(w.state, active, n, nullptr, w.twN, w.tw2, p->tune, st,
-                                    w.wtab, (size_t)s * n * n));
+      if (s > 0)
+        LAUNCH(p, st, "row_pass",
+               prism::launch_row_pass(w.state, active, n, nullptr, w.twN, w.tw2, p->tune, st,
+                                      nullptr, w.wtab, (size_t)s * n * n));
       LAUNCH(p, st, "col_pass",
              prism::launch_col_pass(w.state, active, n, w.prop + (size_t)s * n, w.twN, w.tw2,
                                     p->tune, st));

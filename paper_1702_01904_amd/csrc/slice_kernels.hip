@@ -12,6 +12,7 @@
 
 #include "fft_lds.hpp"
 #include "fft_reg.hpp"
+#include "fft_steps.hpp"
 #include "kernels.hpp"
 
 namespace prism {
@@ -19,24 +20,15 @@ namespace prism {
 namespace {
 
 // Launch shapes (tuned on MI355X; overridable at build time).
-#ifndef PRISM_ROW_ELEMS
-#define PRISM_ROW_ELEMS 2048   // complex values per row-pass workgroup
-#endif
 #ifndef PRISM_COL_E
-#define PRISM_COL_E 8          // complex values per column-pass thread
+#define PRISM_COL_E 8          // complex values per detector column-pass thread
 #endif
-#ifndef PRISM_COL_WPE
-#define PRISM_COL_WPE 1        // minimum waves per SIMD for the column pass
-#endif
-
-constexpr int kRowNT = PRISM_ROW_ELEMS / 8;
 
 // Largest power of two p with p n <= cap (at least 1): rows per workgroup
 // that divide every wave's n rows (n = 2^k, 3 2^k or 9 2^k).
 __host__ __device__ constexpr int pow2_rows(int n, int cap) {
   return 2 * n <= cap ? 2 * pow2_rows(2 * n, cap) : 1;
 }
-__host__ __device__ constexpr int row_nseq(int n) { return pow2_rows(n, PRISM_ROW_ELEMS); }
 __host__ __device__ constexpr int col_tc(int n) { return 8; }
 __host__ __device__ constexpr int col_nt(int n) {
   return (col_tc(n) * n / PRISM_COL_E) < 64
@@ -97,116 +89,6 @@ __global__ void k_prop_lut(float2* lut, int n, int H, const double* __restrict__
   lut[i] = make_float2((float)c, (float)s);
 }
 
-// Tilted plane wave exp(2 pi i (m f x + n f y) / n) in compact form:
-// X(y, kx) = n exp(2 pi i ((n f y) mod n) / n) at kx = m f, zero elsewhere.
-__global__ void k_beam_init(float2* __restrict__ state, const int32_t* __restrict__ mn, int b0,
-                            int nb, int n, int f, const float2* __restrict__ twN) {
-  const int h2 = n / 2;
-  const size_t total = (size_t)nb * n * h2;
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const int w = (int)(i / ((size_t)n * h2));
-  const int rem = (int)(i % ((size_t)n * h2));
-  const int y = rem / h2, jj = rem % h2;
-  const int m = mn[2 * (b0 + w)], nn = mn[2 * (b0 + w) + 1];
-  const int kx = m * f;
-  const int jj0 = kx >= 0 ? kx : kx + h2;
-  float2 v = make_float2(0.f, 0.f);
-  if (jj == jj0) {
-    long long idx = ((long long)nn * f * y) % n;
-    if (idx < 0) idx += n;
-    const float2 t = twN[idx];  // exp(-2 pi i idx / n)
-    v = make_float2(t.x * (float)n, -t.y * (float)n);
-  }
-  state[i] = v;
-}
-
-// ---------------------------------------------------------------------------
-// Row pass: NSEQ rows of length n per workgroup (PRISM_ROW_ELEMS complex in
-// LDS). The inverse x-transform runs 8, 8^MID, RL and the forward one
-// RL, 8^MID, 8 (PairedPlan): the inverse's first stage reads the compact row
-// straight from HBM (its inputs at |kx| >= n/4 are zero), its last stage
-// stays in registers, is multiplied by t_p / n and feeds the forward's first
-// stage, and the forward's last stage stores only the kept half band.
-// WT: each wave w reads its own transmission wtrans[w] + soff (waves of
-// several specimens in one launch); otherwise every wave reads trans.
-template <int N, bool WT>
-__global__ __launch_bounds__(kRowNT) void k_row_pass(float2* __restrict__ state,
-                                                     const float2* __restrict__ trans,
-                                                     const float2* const* __restrict__ wtrans,
-                                                     size_t soff,
-                                                     const float2* __restrict__ twN) {
-  constexpr int NT = kRowNT;
-  constexpr int NSEQ = row_nseq(N);
-  constexpr int H2 = N / 2, E8 = N / 8;
-  using B = RowBatch<N, NSEQ>;
-  using PP = PairedPlan<N>;
-  constexpr int RL = PP::RL, NSL = N / PP::RL;
-  using S8 = StageShape<B, 8, NT>;
-  using SL = StageShape<B, RL, NT>;
-  __shared__ float2 lds[lds_padded(NSEQ * N)];
-  __shared__ float2 tw[N];
-  const int tid = threadIdx.x;
-  const size_t row0 = (size_t)blockIdx.x * NSEQ;
-  load_twiddles<N, NT>(tw, twN, tid);
-  {
-    // inverse, first stage (span 1): inputs j + r n/8, nonzero for r in {0,1,6,7}
-    float2 v[S8::PER][8];
-#pragma unroll
-    for (int p = 0; p < S8::PER; ++p) {
-      const int b = tid + p * NT;
-      v[p][2] = v[p][3] = v[p][4] = v[p][5] = make_float2(0.f, 0.f);
-      if (S8::GUARD && b >= S8::TOT) continue;  // no butterfly (stage_out skips it too)
-      int sq, j;
-      stage_coords<B, S8::NB>(b, sq, j);
-      const float2* src = state + (row0 + sq) * H2 + j;
-      v[p][0] = src[0];
-      v[p][1] = src[E8];
-      v[p][6] = src[2 * E8];
-      v[p][7] = src[3 * E8];
-    }
-    stage_out<B, 8, 1, NT, true>(lds, tid, v);
-  }
-  __syncthreads();
-  fft_radix8_run<B, NT, true, 8, PP::MID>(lds, tw, tid);
-  float2 v[SL::PER][RL];
-  stage_in<B, RL, NSL, NT, true>(lds, tw, tid, v);
-#pragma unroll
-  for (int p = 0; p < SL::PER; ++p) {
-    const int b = tid + p * NT;
-    if (SL::GUARD && b >= SL::TOT) continue;
-    int sq, j;
-    stage_coords<B, SL::NB>(b, sq, j);
-    dft<RL, true>(v[p]);
-    const float2* tb = WT ? wtrans[(row0 + sq) / N] + soff : trans;
-    const float2* t = tb + (size_t)((row0 + sq) % (size_t)N) * N + j;
-#pragma unroll
-    for (int r = 0; r < RL; ++r) v[p][r] = cmul(v[p][r], t[r * NSL]);
-  }
-  __syncthreads();
-  stage_out<B, RL, 1, NT, false>(lds, tid, v);
-  __syncthreads();
-  fft_radix8_run<B, NT, false, RL, PP::MID>(lds, tw, tid);
-  {
-    // forward, last stage (span n/8): outputs j + r n/8, kept for r in {0,1,6,7}
-    float2 w[S8::PER][8];
-    stage_in<B, 8, E8, NT, false>(lds, tw, tid, w);
-#pragma unroll
-    for (int p = 0; p < S8::PER; ++p) {
-      const int b = tid + p * NT;
-      if (S8::GUARD && b >= S8::TOT) continue;
-      int sq, j;
-      stage_coords<B, S8::NB>(b, sq, j);
-      dft8<false>(w[p]);
-      float2* dst = state + (row0 + sq) * H2 + j;
-      dst[0] = w[p][0];
-      dst[E8] = w[p][1];
-      dst[2 * E8] = w[p][6];
-      dst[3 * E8] = w[p][7];
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Four-step row pass for n = R^2 (R = 16, 32). Row element x = R a + b sits
 // with lane b (R lanes per row, 64 / R rows per wave):
@@ -219,9 +101,9 @@ __global__ __launch_bounds__(kRowNT) void k_row_pass(float2* __restrict__ state,
 //            stores the outputs e + R g with |kx| < n/4.
 // Each wave owns its LDS rows, so the transposes need only wave-level
 // ordering. Each lane keeps its R - 1 twiddles w_n^{jc} in registers for the
-// whole kernel (no table reads between the transforms). A workgroup walks
-// `iters` row groups; each wave loads the next row's inputs and the current
-// row's t_p while it computes.
+// whole kernel (no table reads between the transforms). A workgroup walks row
+// groups (gridDim.x apart); each wave loads the next row's inputs and the
+// current row's t_p while it computes.
 
 // Raw buffer resource over count complex values at p (gfx9 word 3), and
 // 8-byte loads / stores at vector offset voff + scalar offset soff (bytes).
@@ -238,20 +120,37 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned vof
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(int2v, v), r, voff, soff, 0);
 }
 
-// Orders LDS accesses of one wave (compiler barrier; LDS executes a wave's
-// instructions in order).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// Row y of plane wave w of a build in compact form: exp(2 pi i (m f x + n f
+// y) / n) has X(y, kx) = n exp(2 pi i ((n f y) mod n) / n) at kx = m f and
+// zero elsewhere. k = kx mod n. The first row pass of a build forms its
+// inputs from this instead of reading a written state: one read and one
+// write of the state less per build.
+struct PlaneRow {
+  int k;
+  float2 z;
+};
+template <int N>
+__device__ __forceinline__ PlaneRow row_wave(const BeamWaves& beams, int w, int y,
+                                             const float2* __restrict__ twN) {
+  const int kx = beams.mn[2 * (beams.b0 + w)] * beams.f;
+  const int ky = beams.mn[2 * (beams.b0 + w) + 1] * beams.f;
+  int idx = (ky * y) % N;  // |ky| < n/4, y < n <= 2048: fits 32 bits
+  if (idx < 0) idx += N;
+  const float2 t = twN[idx];  // exp(-2 pi i idx / n)
+  return PlaneRow{kx < 0 ? kx + N : kx, make_float2(t.x * (float)N, -t.y * (float)N)};
 }
 
-template <int R, bool WT>
+// WT: each wave w reads its own transmission wtrans[w] + soff (waves of
+// several specimens in one launch); otherwise every wave reads trans.
+// INIT: first slice of a build, the inputs are plane waves (row_wave).
+template <int R, bool WT, bool INIT>
 __global__ __launch_bounds__(256) void k_row_pass4(float2* __restrict__ state,
                                                    const float2* __restrict__ trans,
                                                    const float2* const* __restrict__ wtrans,
                                                    size_t soff,
-                                                   const float2* __restrict__ tw2, int iters) {
+                                                   const float2* __restrict__ twN,
+                                                   const float2* __restrict__ tw2, BeamWaves beams,
+                                                   int groups) {
   constexpr int N = R * R, H2 = N / 2, Q = R / 4, LS = R + 1;
   constexpr int RPW = 64 / R;             // rows per wave
   constexpr int RS = R * LS + 8;          // LDS row stride (float2)
@@ -260,22 +159,20 @@ __global__ __launch_bounds__(256) void k_row_pass4(float2* __restrict__ state,
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int j = lane % R, rw = lane / R;
   float2* L = lds + (wv * RPW + rw) * RS;
-  const size_t row_base = (size_t)blockIdx.x * (GROUP * iters) + wv * RPW + rw;
-
   float2 s[2 * Q];  // compact inputs of the next row: a < Q, then a >= R - Q
-  // Buffer loads from the workgroup's first row; live == false gives a
+  // Buffer loads from a group's first row; live == false gives a
   // zero-length resource (zeros, no memory traffic).
-  const float2* wg_rows = state + (size_t)blockIdx.x * (GROUP * iters) * H2;
   const unsigned lane_off = (unsigned)(((wv * RPW + rw) * H2 + j) * 8);
-  auto load_src = [&](int it, bool live) {
-    const __amdgpu_buffer_rsrc_t rs = wave_rsrc(wg_rows, live ? GROUP * iters * H2 : 0);
-    const int soff = it * GROUP * H2 * 8;
+  auto load_src = [&](int g, bool live) {
+    const __amdgpu_buffer_rsrc_t rs =
+        wave_rsrc(state + (size_t)g * GROUP * H2, live ? GROUP * H2 : 0);
 #pragma unroll
-    for (int a = 0; a < Q; ++a) s[a] = buf_load(rs, lane_off, soff + R * a * 8);
+    for (int a = 0; a < Q; ++a) s[a] = buf_load(rs, lane_off, R * a * 8);
 #pragma unroll
-    for (int a = 0; a < Q; ++a) s[Q + a] = buf_load(rs, lane_off, soff + (R * (R - Q + a) - H2) * 8);
+    for (int a = 0; a < Q; ++a) s[Q + a] = buf_load(rs, lane_off, (R * (R - Q + a) - H2) * 8);
   };
-  load_src(0, true);
+  int g = blockIdx.x;
+  if constexpr (!INIT) load_src(g, true);
   // this lane's four-step twiddles w_n^{jc}, c = 1 .. R-1 (the same values
   // serve the inverse, conjugated, and the forward transform), held in
   // registers for the whole loop
@@ -287,16 +184,26 @@ __global__ __launch_bounds__(256) void k_row_pass4(float2* __restrict__ state,
   // carries no pending load and never waits for the previous row's stores
   __builtin_amdgcn_s_waitcnt(0x0F70);
 #pragma unroll 1
-  for (int it = 0; it < iters; ++it) {
-    const size_t row = row_base + (size_t)it * GROUP;
+  for (; g < groups; g += gridDim.x) {
+    const size_t row = (size_t)g * GROUP + wv * RPW + rw;
     float2 v[R];
+    if constexpr (INIT) {
+      const PlaneRow pr = row_wave<N>(beams, (int)(row / N), (int)(row & (size_t)(N - 1)), twN);
 #pragma unroll
-    for (int a = 0; a < R; ++a)
-      v[a] = a < Q ? s[a] : (a >= R - Q ? s[a - (R - 2 * Q)] : make_float2(0.f, 0.f));
-    // Next row's inputs first, then this row's t_p: both are waited for
-    // together at the t_p product, after the inverse transform, so no load
-    // is still pending (and no store waited for) at the top of the loop.
-    load_src(min(it + 1, iters - 1), it + 1 < iters);
+      for (int a = 0; a < R; ++a) {
+        const bool on = (a < Q || a >= R - Q) && R * a + j == pr.k;
+        v[a] = make_float2(on ? pr.z.x : 0.f, on ? pr.z.y : 0.f);
+      }
+    } else {
+#pragma unroll
+      for (int a = 0; a < R; ++a)
+        v[a] = a < Q ? s[a] : (a >= R - Q ? s[a - (R - 2 * Q)] : make_float2(0.f, 0.f));
+      // Next row's inputs first, then this row's t_p: both are waited for
+      // together at the t_p product, after the inverse transform, so no load
+      // is still pending (and no store waited for) at the top of the loop.
+      const int gn = g + (int)gridDim.x;
+      load_src(min(gn, groups - 1), gn < groups);
+    }
     float2 tt[R];
     {
       const float2* tb = WT ? wtrans[row / N] + soff : trans;
@@ -342,7 +249,7 @@ __global__ __launch_bounds__(256) void k_row_pass4(float2* __restrict__ state,
 //   inverse : lane (k1, c) transforms over k2 (inputs outside the half band
 //             are zero), twiddles by w_n^{-k1 m1}, LDS transpose, lane
 //             (m1, c) transforms over k1 and stores y = m1 + R m2.
-// A workgroup walks `iters` tiles, loading the next tile while it
+// A workgroup walks tiles (gridDim.x apart), loading the next tile while it
 // computes the current one.
 #ifndef PRISM_COL4_TC32
 #define PRISM_COL4_TC32 16   // columns per tile at n = 1024
@@ -351,7 +258,7 @@ __global__ __launch_bounds__(256) void k_row_pass4(float2* __restrict__ state,
 template <int R, int TC>
 __global__ __launch_bounds__(TC * R) __attribute__((amdgpu_waves_per_eu(2))) void k_col_pass4(float2* __restrict__ state,
                                                    const float2* __restrict__ prop,
-                                                   const float2* __restrict__ tw2, int iters) {
+                                                   const float2* __restrict__ tw2, int tiles) {
   constexpr int N = R * R, H2 = N / 2, Q = R / 4, LS = R + 1;
   constexpr int NT = TC * R;
   constexpr int TILES = H2 / TC;         // tiles per wave
@@ -381,22 +288,20 @@ __global__ __launch_bounds__(TC * R) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll
     for (int a = 0; a < R; ++a) s[a] = buf_load(rs, lane_off, (c0 + R * a * H2) * 8);
   };
-  // Iteration it handles tile it * gridDim.x + g, with g the XCD-grouped
-  // workgroup index: workgroups resident on one XCD at the same time take
+  // Tiles g, g + gridDim.x, ..., with g the XCD-grouped workgroup index: workgroups resident on one XCD at the same time take
   // adjacent tiles, which share the 128-byte lines of every row.
   const int g = xcd_tile(blockIdx.x, gridDim.x), nwg = gridDim.x;
   load_tile(g, true);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): no load pending at the loop head
   __syncthreads();
 #pragma unroll 1
-  for (int it = 0; it < iters; ++it) {
-    const int tile = it * nwg + g;
+  for (int tile = g; tile < tiles; tile += nwg) {
     const int w = tile / TILES, c0 = (tile % TILES) * TC;
     float2 v[R];
 #pragma unroll
     for (int a = 0; a < R; ++a) v[a] = s[a];
     // the next tile is in flight during this one
-    load_tile(min(it + 1, iters - 1) * nwg + g, it + 1 < iters);
+    load_tile(min(tile + nwg, tiles - 1), tile + nwg < tiles);
     dft_reg<R, false>(v);
 #pragma unroll
     for (int k1 = 0; k1 < R; ++k1) L[k1 * LS + b] = v[k1];
@@ -470,16 +375,186 @@ __global__ __launch_bounds__(TC * R) __attribute__((amdgpu_waves_per_eu(2))) voi
 }
 
 // ---------------------------------------------------------------------------
-// Column pass over a tile of TC adjacent compact columns, held [y][c]. The
-// forward y-transform reads straight from HBM, its last stage stays in
-// registers for the propagator and band limit, and the inverse's last stage
-// stores straight to HBM (PairedPlan order, as in the row pass).
-// DETECT: last multislice slice; instead of the inverse transform, form
-// I = |Psi|^2 / n^2 and write per-tile detector partial sums.
-template <int N, bool DETECT>
-__global__ __launch_bounds__(col_nt(N)) __attribute__((amdgpu_waves_per_eu(PRISM_COL_WPE)))
-void k_col_pass(float2* __restrict__ state, const float2* __restrict__ prop,
-                const float2* __restrict__ twN, DetBins bins, double* __restrict__ partial) {
+// Row pass for the grids that are not a square of a register DFT length
+// (fft_steps.hpp: three or two register DFT steps per transform, one LDS
+// exchange between them). L lanes hold a row:
+//   inverse: comb order in (only |kx| < n/4, i.e. registers a < R1/4 and
+//            a >= 3 R1/4, are nonzero), block order out;
+//   t_p / n multiplies psi in registers;
+//   forward: block order in, comb order out, the half band stored.
+// Twiddles stay in registers for the whole kernel; a workgroup walks row
+// groups (gridDim.x apart) with the next group's inputs and the current
+// group's t_p in flight during the transforms.
+// Bound: VALU issue (n = 1536: 68 VALU instructions per row element, issue
+// near 100 % busy at two waves per SIMD while the state stays in the Infinity
+// Cache). R1 values per lane keep the exchanges at two per transform, against
+// three LDS round trips and a workgroup barrier pair each for the radix-8 LDS
+// stages this replaces: 99 instead of 209 us per 20- and 27-wave launch at n =
+// 1536 (3.8 against 2.6 TB/s), 123 instead of 208 us for 11 and 14 waves at n
+// = 2048.
+// WT and INIT as in the four-step pass.
+template <int N, bool WT, bool INIT>
+__global__ __launch_bounds__(GridSteps<N>::ROW_NT) __attribute__((amdgpu_waves_per_eu(2)))
+void k_row_steps(float2* __restrict__ state, const float2* __restrict__ trans,
+                 const float2* const* __restrict__ wtrans, size_t soff,
+                 const float2* __restrict__ twN, BeamWaves beams, int groups) {
+  using GS = GridSteps<N>;
+  using ST = typename GS::Row;
+  constexpr int H2 = N / 2, R1 = ST::R1, L = ST::L, Q = R1 / 4, D = ST::D, MB = ST::MB;
+  constexpr int GROUP = GS::ROW_NT / L;  // rows per workgroup iteration
+  static_assert(N % GROUP == 0, "a row group lies inside one wave function");
+  __shared__ float2 lds[GROUP * GS::ROW_RS];
+  __shared__ float2 tab[ST::TLN];
+  const int tid = threadIdx.x, b = tid % L, rw = tid / L;
+  float2* Lr = lds + rw * GS::ROW_RS;
+  const unsigned row_off = (unsigned)(rw * H2 + b) * 8u, t_off = (unsigned)(rw * N + b) * 8u;
+
+  float2 s[2 * Q];  // compact inputs of the next row: a < Q, then a >= R1 - Q
+  auto load_src = [&](int g, bool live) {
+    const __amdgpu_buffer_rsrc_t rs =
+        wave_rsrc(state + (size_t)g * GROUP * H2, live ? GROUP * H2 : 0);
+#pragma unroll
+    for (int a = 0; a < Q; ++a) s[a] = buf_load(rs, row_off, L * a * 8);
+#pragma unroll
+    for (int a = 0; a < Q; ++a) s[Q + a] = buf_load(rs, row_off, (L * (R1 - Q + a) - H2) * 8);
+  };
+  int g = blockIdx.x;
+  if constexpr (!INIT) load_src(g, true);
+  typename ST::Tw tw;
+  ST::load_twiddles(twN, b, tab, tid, GS::ROW_NT, tw);
+  if constexpr (!INIT) settle(s);
+  if constexpr (ST::TLDS) __syncthreads();
+#pragma unroll 1
+  for (; g < groups; g += gridDim.x) {
+    const int w = g * GROUP / N, y0 = g * GROUP - w * N;  // uniform
+    float2 v[R1];
+    if constexpr (INIT) {
+      const PlaneRow pr = row_wave<N>(beams, w, y0 + rw, twN);
+#pragma unroll
+      for (int a = 0; a < R1; ++a) {
+        const bool on = (a < Q || a >= R1 - Q) && L * a + b == pr.k;
+        v[a] = make_float2(on ? pr.z.x : 0.f, on ? pr.z.y : 0.f);
+      }
+    } else {
+#pragma unroll
+      for (int a = 0; a < R1; ++a)
+        v[a] = a < Q ? s[a] : (a >= R1 - Q ? s[a - (R1 - 2 * Q)] : make_float2(0.f, 0.f));
+      const int gn = g + (int)gridDim.x;
+      load_src(min(gn, groups - 1), gn < groups);
+    }
+    float2 tt[R1];
+    {
+      const float2* tb = (WT ? wtrans[w] + soff : trans) + (size_t)y0 * N;
+      const __amdgpu_buffer_rsrc_t rt = wave_rsrc(tb, GROUP * N);
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int d = 0; d < D; ++d) tt[i * D + d] = buf_load(rt, t_off, (L * i + N / D * d) * 8);
+    }
+    if constexpr (!(ST::TWO && R1 == 32))  // (no registers left for it)
+      __builtin_amdgcn_sched_barrier(0);   // the loads go out before the first transform
+    ST::template comb_to_block<true>(v, Lr, b, tw);
+#pragma unroll
+    for (int e = 0; e < R1; ++e) v[e] = cmul(v[e], tt[e]);
+    ST::template block_to_comb<false>(v, Lr, b, tw);
+    const __amdgpu_buffer_rsrc_t rd = wave_rsrc(state + (size_t)g * GROUP * H2, GROUP * H2);
+#pragma unroll
+    for (int a = 0; a < R1; ++a) {
+      if (a < Q) buf_store(rd, row_off, L * a * 8, v[a]);
+      else if (a >= R1 - Q) buf_store(rd, row_off, (L * a - H2) * 8, v[a]);
+    }
+  }
+}
+
+// Column pass of the same grids over tiles of TC adjacent compact columns
+// (lane (b, c) = (tid / TC, tid % TC)): forward y-transform from comb to
+// block order, P_p(kx) P_p(ky) M / n in registers with the rows |ky| >= n/4
+// cut, inverse back to comb order. Workgroups walk tiles (gridDim.x apart,
+// XCD-grouped as in the four-step pass) with the next tile in flight.
+// Bound: the workgroup's phases (loads, VALU, LDS exchanges) overlap only
+// through the prefetch, since one workgroup fills a compute unit's registers
+// (n = 1536: VALU 49 % busy, 3.6 TB/s); 102 instead of 174 us per 20- and
+// 27-wave launch at n = 1536, 101 instead of 155 us for 11 and 14 waves at n =
+// 2048, against the radix-8 LDS stages this replaces.
+template <int N>
+__global__ __launch_bounds__(GridSteps<N>::TC * GridSteps<N>::L)
+__attribute__((amdgpu_waves_per_eu(2))) void k_col_steps(float2* __restrict__ state,
+                                                         const float2* __restrict__ prop,
+                                                         const float2* __restrict__ twN,
+                                                         int tiles) {
+  using GS = GridSteps<N>;
+  using ST = typename GS::Col;
+  constexpr int H2 = N / 2, R1 = ST::R1, L = ST::L, D = ST::D, MB = ST::MB, QD = D / 4;
+  constexpr int TC = GS::TC, NT = TC * L, TILES = H2 / TC;
+  static_assert(H2 % TC == 0, "whole tiles");
+  __shared__ float2 pyl[H2];  // P_p(ky) for |ky| < n/4, compact order
+  __shared__ float2 lds[TC * GS::COL_RS];
+  __shared__ float2 tab[ST::TLN];
+  const int tid = threadIdx.x, c = tid % TC, b = tid / TC;
+  for (int i = tid; i < H2; i += NT) pyl[i] = prop[i < H2 / 2 ? i : i + H2];
+  float2* Lc = lds + c * GS::COL_RS;
+  const float inv_n = 1.0f / (float)N;
+  const unsigned lane_off = (unsigned)(b * H2 + c) * 8u;
+  float2 s[R1];  // next tile's column elements y = L a + b
+  auto load_tile = [&](int tile, bool live) {
+    const int w = tile / TILES, c0 = (tile % TILES) * TC;
+    const __amdgpu_buffer_rsrc_t rs =
+        wave_rsrc(state + (size_t)w * N * H2, live ? N * H2 : 0);
+#pragma unroll
+    for (int a = 0; a < R1; ++a) s[a] = buf_load(rs, lane_off, (c0 + L * a * H2) * 8);
+  };
+  int tile = xcd_tile(blockIdx.x, gridDim.x);
+  load_tile(tile, true);
+  typename ST::Tw tw;
+  ST::load_twiddles(twN, b, tab, tid, NT, tw);
+  settle(s);
+  __syncthreads();
+#pragma unroll 1
+  for (; tile < tiles; tile += gridDim.x) {
+    const int w = tile / TILES, c0 = (tile % TILES) * TC;
+    float2 v[R1];
+#pragma unroll
+    for (int a = 0; a < R1; ++a) v[a] = s[a];
+    const int next = tile + (int)gridDim.x;
+    load_tile(min(next, tiles - 1), next < tiles);
+    if constexpr (!(ST::TWO && R1 == 32))  // (no registers left for it)
+      __builtin_amdgcn_sched_barrier(0);   // the loads go out before the first transform
+    ST::template comb_to_block<false>(v, Lc, b, tw);
+    const int jj = c0 + c;
+    const int kx = jj < H2 / 2 ? jj : jj - H2;
+    const float2 px = cscale(pyl[jj], inv_n);
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        if (d < QD || d >= D - QD) {
+          const int kyi = b + L * i + N / D * d;
+          const int ky = d < QD ? kyi : kyi - N;
+          const float2 m = cmul(cmul(v[i * D + d], px), pyl[d < QD ? kyi : kyi - H2]);
+          const bool keep = 16 * (kx * kx + ky * ky) < N * N;
+          v[i * D + d] = make_float2(keep ? m.x : 0.f, keep ? m.y : 0.f);
+        } else {
+          v[i * D + d] = make_float2(0.f, 0.f);
+        }
+      }
+    ST::template block_to_comb<true>(v, Lc, b, tw);
+    const __amdgpu_buffer_rsrc_t rd = wave_rsrc(state + (size_t)w * N * H2, N * H2);
+#pragma unroll
+    for (int a = 0; a < R1; ++a) buf_store(rd, lane_off, (c0 + L * a * H2) * 8, v[a]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Last column pass of multislice over a tile of TC adjacent compact columns,
+// held [y][c] in LDS: the forward y-transform reads straight from HBM, its
+// last stage stays in registers for the propagator and band limit, then
+// I = |Psi|^2 / n^2 gives per-tile detector partial sums.
+template <int N>
+__global__ __launch_bounds__(col_nt(N)) void k_col_detect(const float2* __restrict__ state,
+                                                          const float2* __restrict__ prop,
+                                                          const float2* __restrict__ twN,
+                                                          DetBins bins,
+                                                          double* __restrict__ partial) {
   constexpr int TC = col_tc(N), NT = col_nt(N);
   constexpr int H2 = N / 2, Q = N / 4, E8 = N / 8;
   constexpr int TILES = H2 / TC;
@@ -494,7 +569,7 @@ void k_col_pass(float2* __restrict__ state, const float2* __restrict__ prop,
   const int tid = threadIdx.x;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int w = tile / TILES, c0 = (tile % TILES) * TC;
-  float2* base = state + (size_t)w * N * H2 + c0;
+  const float2* base = state + (size_t)w * N * H2 + c0;
   load_twiddles<N, NT>(tw, twN, tid);
   {
     float2 v[S8::PER][8];
@@ -513,7 +588,6 @@ void k_col_pass(float2* __restrict__ state, const float2* __restrict__ prop,
   fft_radix8_run<B, NT, false, 8, PP::MID>(lds, tw, tid);
   float2 v[SL::PER][RL];
   stage_in<B, RL, NSL, NT, false>(lds, tw, tid, v);
-  const float inv_n = 1.0f / (float)N;
 #pragma unroll
   for (int p = 0; p < SL::PER; ++p) {
     const int b = tid + p * NT;
@@ -530,70 +604,50 @@ void k_col_pass(float2* __restrict__ state, const float2* __restrict__ prop,
       const int ky = signed_k(yi, N);
       const int k2 = kx * kx + ky * ky;
       if (16 * k2 < N * N) {
-        float2 z = cmul(cmul(v[p][r], px), prop[yi]);
-        v[p][r] = DETECT ? z : cscale(z, inv_n);
+        v[p][r] = cmul(cmul(v[p][r], px), prop[yi]);
       } else {
         v[p][r] = make_float2(0.f, 0.f);
       }
     }
   }
-  if constexpr (!DETECT) {
-    __syncthreads();
-    stage_out<B, RL, 1, NT, true>(lds, tid, v);
-    __syncthreads();
-    fft_radix8_run<B, NT, true, RL, PP::MID>(lds, tw, tid);
-    float2 u[S8::PER][8];
-    stage_in<B, 8, E8, NT, true>(lds, tw, tid, u);
+  __shared__ double red[8][NW];
+  const double inv_n2 = 1.0 / ((double)N * (double)N);
+  for (int j0 = 0; j0 < bins.n; j0 += 8) {
+    double acc[8];
 #pragma unroll
-    for (int p = 0; p < S8::PER; ++p) {
+    for (int q = 0; q < 8; ++q) acc[q] = 0.0;
+#pragma unroll
+    for (int p = 0; p < SL::PER; ++p) {
       const int b = tid + p * NT;
-      if (S8::GUARD && b >= S8::TOT) continue;
+      if (SL::GUARD && b >= SL::TOT) continue;
       int c, j;
-      stage_coords<B, S8::NB>(b, c, j);
-      dft8<true>(u[p]);
+      stage_coords<B, SL::NB>(b, c, j);
+      const int jj = c0 + c;
+      const int kx = jj < Q ? jj : jj - H2;
 #pragma unroll
-      for (int r = 0; r < 8; ++r) base[(size_t)(j + r * E8) * H2 + c] = u[p][r];
-    }
-  } else {
-    __shared__ double red[8][NW];
-    const double inv_n2 = 1.0 / ((double)N * (double)N);
-    for (int j0 = 0; j0 < bins.n; j0 += 8) {
-      double acc[8];
+      for (int r = 0; r < RL; ++r) {
+        const int ky = signed_k(j + r * NSL, N);
+        const int k2 = kx * kx + ky * ky;
+        const double I = ((double)v[p][r].x * v[p][r].x + (double)v[p][r].y * v[p][r].y) * inv_n2;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) acc[q] = 0.0;
-#pragma unroll
-      for (int p = 0; p < SL::PER; ++p) {
-        const int b = tid + p * NT;
-        if (SL::GUARD && b >= SL::TOT) continue;
-        int c, j;
-        stage_coords<B, SL::NB>(b, c, j);
-        const int jj = c0 + c;
-        const int kx = jj < Q ? jj : jj - H2;
-#pragma unroll
-        for (int r = 0; r < RL; ++r) {
-          const int ky = signed_k(j + r * NSL, N);
-          const int k2 = kx * kx + ky * ky;
-          const double I = ((double)v[p][r].x * v[p][r].x + (double)v[p][r].y * v[p][r].y) * inv_n2;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const int jb = j0 + q;
-            if (jb < bins.n && k2 >= bins.lo[jb] && k2 < bins.hi[jb]) acc[q] += I;
-          }
+        for (int q = 0; q < 8; ++q) {
+          const int jb = j0 + q;
+          if (jb < bins.n && k2 >= bins.lo[jb] && k2 < bins.hi[jb]) acc[q] += I;
         }
       }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const double sum = wave_sum(acc[q]);
-        if ((tid & 63) == 0) red[q][tid >> 6] = sum;
-      }
-      __syncthreads();
-      if (tid < 8 && j0 + tid < bins.n) {
-        double sum = 0.0;
-        for (int wv = 0; wv < NW; ++wv) sum += red[tid][wv];
-        partial[((size_t)w * TILES + (tile % TILES)) * bins.n + j0 + tid] = sum;
-      }
-      __syncthreads();
     }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const double sum = wave_sum(acc[q]);
+      if ((tid & 63) == 0) red[q][tid >> 6] = sum;
+    }
+    __syncthreads();
+    if (tid < 8 && j0 + tid < bins.n) {
+      double sum = 0.0;
+      for (int wv = 0; wv < NW; ++wv) sum += red[tid][wv];
+      partial[((size_t)w * TILES + (tile % TILES)) * bins.n + j0 + tid] = sum;
+    }
+    __syncthreads();
   }
 }
 
@@ -720,14 +774,6 @@ hipError_t launch_prop_lut(float2* lut, int n, int H, const double* thick_dev, d
   return hipGetLastError();
 }
 
-hipError_t launch_beam_init(float2* state, const int32_t* beams_mn, int b0, int nb, int n, int f,
-                            const float2* twN, hipStream_t st) {
-  const size_t total = (size_t)nb * n * (n / 2);
-  hipLaunchKernelGGL(k_beam_init, dim3(blocks_for(total, 256)), dim3(256), 0, st, state, beams_mn,
-                     b0, nb, n, f, twN);
-  return hipGetLastError();
-}
-
 #define PRISM_DISPATCH_N(n, CALL) \
   switch (n) {                    \
     case 128: CALL(128); break;   \
@@ -744,6 +790,21 @@ hipError_t launch_beam_init(float2* state, const int32_t* beams_mn, int b0, int 
     default: return hipErrorInvalidValue; \
   }
 
+// The grids of k_row_steps / k_col_steps.
+#define PRISM_DISPATCH_STEPS(n, CALL) \
+  switch (n) {                        \
+    case 128: CALL(128); break;       \
+    case 192: CALL(192); break;       \
+    case 384: CALL(384); break;       \
+    case 512: CALL(512); break;       \
+    case 576: CALL(576); break;       \
+    case 768: CALL(768); break;       \
+    case 1152: CALL(1152); break;     \
+    case 1536: CALL(1536); break;     \
+    case 2048: CALL(2048); break;     \
+    default: return hipErrorInvalidValue; \
+  }
+
 hipError_t launch_twiddles2(float2* tw2, int n, hipStream_t st) {
   const int R = four_step_radix(n);
   if (R == 0) return hipSuccess;
@@ -753,48 +814,60 @@ hipError_t launch_twiddles2(float2* tw2, int n, hipStream_t st) {
 
 int four_step_radix(int n) { return n == 1024 ? 32 : (n == 256 ? 16 : 0); }
 
-// Largest power of two <= maxit dividing units with units / it >= min_wgs
-// (1 if none).
-static int pick_iters(int units, int maxit, int min_wgs) {
-  int it = maxit;
-  while (it > 1 && (units % it != 0 || units / it < min_wgs)) it /= 2;
-  return it;
+// Workgroups of a slice-pass launch over `units` row groups or tiles: the 256
+// compute units times the workgroups one holds (per_cu), so that every
+// workgroup walks units / grid of them and no last round runs nearly empty;
+// a whole multiple of that where one would walk over maxit units or fewer
+// than min_wgs would be launched; at most one per unit.
+static unsigned pass_grid(int units, int per_cu, int maxit, int min_wgs) {
+  const long long slots = 256LL * per_cu;
+  const long long rounds = std::max((units + slots * maxit - 1) / (slots * maxit),
+                                    (min_wgs + slots - 1) / slots);
+  return (unsigned)std::min<long long>(units, slots * rounds);
 }
 
 hipError_t launch_row_pass(float2* state, int nwaves, int n, const float2* trans_p,
                            const float2* twN, const float2* tw2, const LaunchTuning& tune,
-                           hipStream_t st, const float2* const* wtrans, size_t soff) {
-  // row groups of 4 waves x 64/R rows; the iteration count is the largest
-  // power of two (up to tune.row_iters) that divides them and still leaves
-  // tune.row_min_wg workgroups
+                           hipStream_t st, const BeamWaves* init, const float2* const* wtrans,
+                           size_t soff) {
   const bool wt = wtrans != nullptr;
+  const BeamWaves bw = init ? *init : BeamWaves{nullptr, 0, 0};
+  if (init && wt) return hipErrorInvalidValue;  // first slices run one specimen at a time
   if (n == 1024 || n == 256) {
+    // row groups of 4 waves x 64/R rows; two (R = 32) or three workgroups fit
+    // a compute unit's registers
     const int R = n == 1024 ? 32 : 16;
     const int groups = nwaves * n / (4 * 64 / R);
-    const int it = pick_iters(groups, tune.row_iters, tune.row_min_wg);
-    const dim3 grid((unsigned)(groups / it));
-#define ROW4(RR, WW)                                                                            \
-  hipLaunchKernelGGL((k_row_pass4<RR, WW>), grid, dim3(256), 0, st, state, trans_p, wtrans, soff, \
-                     tw2, it)
+    const dim3 grid(pass_grid(groups, R == 32 ? 2 : 3, tune.row_iters, tune.row_min_wg));
+#define ROW4(RR, WW, II)                                                                      \
+  hipLaunchKernelGGL((k_row_pass4<RR, WW, II>), grid, dim3(256), 0, st, state, trans_p, wtrans, \
+                     soff, twN, tw2, bw, groups)
     if (R == 32) {
-      if (wt) ROW4(32, true); else ROW4(32, false);
+      if (init) ROW4(32, false, true);
+      else if (wt) ROW4(32, true, false);
+      else ROW4(32, false, false);
     } else {
-      if (wt) ROW4(16, true); else ROW4(16, false);
+      if (init) ROW4(16, false, true);
+      else if (wt) ROW4(16, true, false);
+      else ROW4(16, false, false);
     }
 #undef ROW4
     return hipGetLastError();
   }
-#define ROW(NN)                                                                                 \
-  if (wt)                                                                                       \
-    hipLaunchKernelGGL((k_row_pass<NN, true>),                                                  \
-                       dim3((unsigned)((size_t)nwaves * NN / row_nseq(NN))), dim3(kRowNT), 0,   \
-                       st, state, trans_p, wtrans, soff, twN);                                  \
-  else                                                                                          \
-    hipLaunchKernelGGL((k_row_pass<NN, false>),                                                 \
-                       dim3((unsigned)((size_t)nwaves * NN / row_nseq(NN))), dim3(kRowNT), 0,   \
-                       st, state, trans_p, wtrans, soff, twN)
-  PRISM_DISPATCH_N(n, ROW)
+#define ROW1(NN, WW, II)                                                                        \
+  hipLaunchKernelGGL((k_row_steps<NN, WW, II>), grid, dim3(GridSteps<NN>::ROW_NT), 0, st, state, \
+                     trans_p, wtrans, soff, twN, bw, groups)
+#define ROW(NN)                                                                                \
+  {                                                                                            \
+    const int groups = nwaves * (NN / (GridSteps<NN>::ROW_NT / GridSteps<NN>::L));             \
+    const dim3 grid(pass_grid(groups, GridSteps<NN>::ROW_WGS, tune.row_iters, tune.row_min_wg)); \
+    if (init) ROW1(NN, false, true);                                                           \
+    else if (wt) ROW1(NN, true, false);                                                        \
+    else ROW1(NN, false, false);                                                               \
+  }
+  PRISM_DISPATCH_STEPS(n, ROW)
 #undef ROW
+#undef ROW1
   return hipGetLastError();
 }
 
@@ -803,27 +876,31 @@ int col_tiles(int n) { return (n / 2) / col_tc(n); }
 hipError_t launch_col_pass(float2* state, int nwaves, int n, const float2* prop_p,
                            const float2* twN, const float2* tw2, const LaunchTuning& tune,
                            hipStream_t st) {
-  // tiles per launch: nwaves x (n/2) / TC, walked up to tune.col_iters at a
-  // time while tune.col_min_wg workgroups remain
   if (n == 1024) {
-    constexpr int TC = PRISM_COL4_TC32, TPW = 512 / TC;
-    const int tiles = nwaves * TPW;
-    const int it = pick_iters(tiles, tune.col_iters, tune.col_min_wg);
-    hipLaunchKernelGGL((k_col_pass4<32, TC>), dim3((unsigned)(tiles / it)), dim3(TC * 32), 0, st,
-                       state, prop_p, tw2, it);
+    constexpr int TC = PRISM_COL4_TC32;
+    const int tiles = nwaves * (512 / TC);
+    hipLaunchKernelGGL((k_col_pass4<32, TC>),
+                       dim3(pass_grid(tiles, 16 / TC, tune.col_iters, tune.col_min_wg)),
+                       dim3(TC * 32), 0, st, state, prop_p, tw2, tiles);
     return hipGetLastError();
   }
   if (n == 256) {
-    const int tiles = nwaves * 8, it = pick_iters(tiles, tune.col_iters, tune.col_min_wg);
-    hipLaunchKernelGGL((k_col_pass4<16, 16>), dim3((unsigned)(tiles / it)), dim3(256), 0, st,
-                       state, prop_p, tw2, it);
+    const int tiles = nwaves * 8;
+    hipLaunchKernelGGL((k_col_pass4<16, 16>),
+                       dim3(pass_grid(tiles, 4, tune.col_iters, tune.col_min_wg)), dim3(256), 0, st,
+                       state, prop_p, tw2, tiles);
     return hipGetLastError();
   }
-  DetBins none{};
-#define COL(NN)                                                                                  \
-  hipLaunchKernelGGL((k_col_pass<NN, false>), dim3((unsigned)(nwaves * col_tiles(NN))),          \
-                     dim3(col_nt(NN)), 0, st, state, prop_p, twN, none, (double*)nullptr)
-  PRISM_DISPATCH_N(n, COL)
+#define COL(NN)                                                                                 \
+  {                                                                                             \
+    const int tiles = nwaves * (NN / 2 / GridSteps<NN>::TC);                                    \
+    hipLaunchKernelGGL((k_col_steps<NN>),                                                       \
+                       dim3(pass_grid(tiles, GridSteps<NN>::COL_WGS, tune.col_iters,           \
+                                       tune.col_min_wg)),                                       \
+                       dim3(GridSteps<NN>::TC * GridSteps<NN>::L), 0, st, state, prop_p, twN,   \
+                       tiles);                                                                  \
+  }
+  PRISM_DISPATCH_STEPS(n, COL)
 #undef COL
   return hipGetLastError();
 }
@@ -832,9 +909,8 @@ hipError_t launch_col_detect(const float2* state, int nwaves, int n, const float
                              const float2* twN, const DetBins& bins, double* partial,
                              hipStream_t st) {
 #define COLD(NN)                                                                                 \
-  hipLaunchKernelGGL((k_col_pass<NN, true>), dim3((unsigned)(nwaves * col_tiles(NN))),           \
-                     dim3(col_nt(NN)), 0, st, const_cast<float2*>(state), prop_p, twN, bins,    \
-                     partial)
+  hipLaunchKernelGGL((k_col_detect<NN>), dim3((unsigned)(nwaves * col_tiles(NN))),               \
+                     dim3(col_nt(NN)), 0, st, state, prop_p, twN, bins, partial)
   PRISM_DISPATCH_N(n, COLD)
 #undef COLD
   return hipGetLastError();
