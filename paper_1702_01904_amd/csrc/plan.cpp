@@ -1195,14 +1195,19 @@ int prism_build_smatrix(prism_plan* p, int f, double amax_mrad, void* S, size_t 
           "copy beam list");
   float2* Sout = static_cast<float2*>(S);
   const size_t splane = (size_t)(n / 2) * (n / 2);
-  // Small builds (at most two chunks of beams, so single launches leave the
-  // GPU partly idle) run in two lanes: the state buffer is split in two and
-  // alternate beam groups run on the caller's stream and on the plan's
-  // second stream, so that one group's VALU-heavy row pass overlaps the
-  // other's memory-bound column pass. Larger builds keep one lane, where
-  // every launch fills the GPU and kernel timings stay exclusive.
-  const int lanes =
-      (PRISM_BUILD_STREAMS > 1 && chunk >= 2 && B > chunk / 2 && B <= 2 * chunk) ? 2 : 1;
+  // Two lanes: the state buffer is split in two and alternate beam groups run
+  // on the caller's stream and on the plan's second stream, so that one
+  // group's VALU-bound row pass overlaps the other's memory-bound column pass
+  // (n = 1024, 373 beams, 12 slices: 15.8 ms against 17.0 on one stream; n =
+  // 2048, 101 beams, 6 slices: 11.4 against 12.1). Forking and joining the
+  // streams costs about 80 us, so builds whose passes move less than 1 GiB
+  // (0.2 ms of HBM) keep one: n = 128, 49 beams, 4 slices (51 MB) take 63 us
+  // on one stream and 140 on two, n = 256, 161 beams, 8 slices (1.3 GB) 370
+  // and 333. Per-kernel timing (prism_profile_enable) also keeps one lane, so
+  // that no time includes a co-running kernel.
+  const double moved = 4.0 * B * p->H * (double)state_bytes(n);
+  const int lanes = (PRISM_BUILD_STREAMS > 1 && !p->prof_on && chunk >= 2 && B >= 2 &&
+                     moved >= (double)(1 << 30)) ? 2 : 1;
   // one chunk: its two halves (the state holds B waves); two: half a chunk each
   const int sub = lanes == 1 ? chunk : (B <= chunk ? (B + 1) / 2 : chunk / 2);
   hipStream_t ls[2] = {st, st};
