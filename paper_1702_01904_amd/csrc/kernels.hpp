@@ -118,8 +118,10 @@ struct ActiveBeam {
 // Probes per group of the packed window sum (they share one union window):
 // the default for window side w.
 int contract_group(int w);
-// Workgroups per probe group along the union tiles (each loops over tiles).
-int contract_tile_slots(int w, int window_tile_div);
+// Workgroups per probe group along the union tiles (each loops over tiles):
+// the tiles of one window / window_tile_div, more where the launch's groups
+// are too few to fill the GPU with that.
+int contract_tile_slots(int w, int window_tile_div, int groups);
 
 // Low-precision probe step (BF16 or FP16 operands, FP32 accumulation).
 // Operand forms of the packed window sum: 16-bit (BF16, FP16; one 32-bit
@@ -129,8 +131,6 @@ enum class Prec { kBF16 = 1, kFP16 = 2, kF32 = 3 };
 constexpr int kC16KB = 32;  // 32-bit words per K block row
 __host__ __device__ constexpr int prec_block_beams(Prec p) { return p == Prec::kF32 ? 16 : 32; }
 __host__ __device__ constexpr int prec_words(Prec p) { return p == Prec::kF32 ? 2 : 1; }
-// Beam rows of the packed S-matrix are padded to a whole pair of K blocks.
-__host__ __device__ constexpr int prec_beam_pad(Prec p) { return 2 * prec_block_beams(p); }
 // scale[a] = 2^-e with e the smallest integer such that every |Re|, |Im| of
 // active beam a's plane is < 2^e (1 for an all-zero plane); partial holds
 // n_act * kScaleSplit floats of per-block maxima (ns >= 64).
@@ -140,8 +140,9 @@ hipError_t launch_s16_scale(const float2* smatrix, const ActiveBeam* act, int n_
 // s16 [ns*ns][n_actp][2] 16-bit: (Re, Im) of scale[a] * S_a(pixel); zero for a >= n_act.
 hipError_t launch_s16_pack(const float2* smatrix, const ActiveBeam* act, int n_act, int n_actp,
                            int ns, const float* scale, void* s16, Prec prec, hipStream_t st);
-// a16: per probe group and 32-beam block, the real-ified A' block [2G][64] in
-// 16 bits of alpha'' = exp(i phase) / scale[a]; also the window origins.
+// a16: per probe group and K block, the A block of alpha'' = exp(i phase)
+// (FP16: / scale[a]) (16 bits: [G][32 beams] words (Re, -Im); FP32: real-ified [2G][32
+// words]); also the window origins.
 hipError_t launch_alpha16(const double* probe_xy, int p0, int np, const ActiveBeam* act,
                           int n_act, int n_actp, int f, int ns, int w, const ProbeOptics& po,
                           const float* scale, int group, void* a16, int2* origin, Prec prec,
@@ -154,7 +155,7 @@ hipError_t launch_alpha16(const double* probe_xy, int p0, int np, const ActiveBe
 constexpr int kMaxSeg = 16;
 struct ContractSeg {
   const uint32_t* s16;  // packed S of its specimen: [ns^2][rowlen] words
-  const uint32_t* a16;  // [groups][K blocks][2G][32 words]
+  const uint32_t* a16;  // [groups][K blocks][2G (16-bit: G)][32 words]
   const int2* origin;   // [np] window origins
   float2* window;       // [np][w][w]
   int rowlen;           // 32-bit words per packed pixel row

@@ -395,9 +395,9 @@ prism::Prec packed_prec(int prec) {
                                  : (prec == PRISM_PREC_FP16 ? prism::Prec::kFP16 : prism::Prec::kF32);
 }
 
-// Active beams padded to a whole pair of K blocks.
+// Active beams padded to whole K blocks.
 int padded_beams(int n_act, prism::Prec pk) {
-  const int pad = prism::prec_beam_pad(pk);
+  const int pad = prism::prec_block_beams(pk);
   return (n_act + pad - 1) / pad * pad;
 }
 
@@ -418,7 +418,7 @@ struct ProbeBatchWs {
   std::vector<PackWs> packs;
   std::vector<uint16_t*> pix;  // per pixel-list set: bins as lists of window pixels
   std::vector<prism::BinLists*> lists;
-  uint32_t* a16;    // packed alpha: [groups][K blocks][2G][32 words]
+  uint32_t* a16;    // packed alpha: [groups][K blocks][2G (16-bit: G)][32 words]
   int2* origin;     // [chunk]
   float2* window;   // [chunk][w][w]
   double* partial;  // W > 128: [chunk][tiles][PRISM_MAX_DET] detector partials

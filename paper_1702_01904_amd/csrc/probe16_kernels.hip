@@ -8,10 +8,12 @@
 //    divided by the same factor, so the product is unchanged in exact
 //    arithmetic and FP16 stays in range.
 //  * S is packed once per call into a pixel-major 16-bit copy
-//    s16[pixel][beam] = (Re, Im), beam rows padded to 64 entries, so that
+//    s16[pixel][beam] = (Re, Im), beam rows padded to whole K blocks, so that
 //    one 32-beam K block of a pixel is 128 contiguous bytes.
-//  * alpha is written by k_alpha16 directly in the real-ified MFMA A layout
-//    (rows 2g: (Re, -Im), rows 2g+1: (Im, Re)) per probe group and K block.
+//  * alpha is written by k_alpha16 directly in the MFMA A layout per probe
+//    group and K block: FP32 real-ified (rows 2g: (Re, -Im), rows 2g+1: (Im,
+//    Re)); 16-bit one row (Re, -Im) per probe, from which the matrix core's
+//    (Im, Re) operand is made in registers (a half swap and a sign).
 //  * v_mfma_f32_16x16x32_{bf16,f16}: lane l holds A[l%16][8(l/16)+j],
 //    B[8(l/16)+j][l%16] (j < 8) and D[4(l/16)+i][l%16] (i < 4).
 //  * FP32: a K block is 16 beams (the same 128 bytes per row). Each lane
@@ -20,7 +22,7 @@
 //    permutation of the block's 32 real K' indices, so the sum is the same.
 //    The scale is 1.
 //  * Staging: 16-bit K blocks pass through registers into padded LDS rows,
-//    two blocks ahead (these sums wait on operand fetch); FP32 K blocks go
+//    two blocks ahead (these sums are bound by operand fetch); FP32 K blocks go
 //    straight from global memory into XOR-swizzled LDS rows
 //    (global_load_lds_dwordx4), one block ahead, which frees the staging
 //    registers for reading both K steps' operands before their products.
@@ -40,6 +42,11 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int wrap_mod16(long long v, int m) {
   long long r = v % m;
   return (int)(r < 0 ? r + m : r);
+}
+
+// Difference d of two origins in [0, ns) (ns even) wrapped to [-ns/2, ns/2).
+__device__ __forceinline__ int wrap_near(int d, int ns) {
+  return d >= ns / 2 ? d - ns : (d < -ns / 2 ? d + ns : d);
 }
 
 template <Prec P>
@@ -175,7 +182,7 @@ __global__ __launch_bounds__(256) void k_s16_pack(const float2* __restrict__ S,
   }
 }
 
-// One thread per (probe group, K block, probe g, beam bl): the A' entries of
+// One thread per (probe group, K block, probe g, beam bl): the A entries of
 // alpha'' = exp(i phase) / scale[a] (scale 1 for FP32), zero outside the
 // probe / beam range.
 template <Prec P>
@@ -214,146 +221,192 @@ __global__ void k_alpha16(const double* __restrict__ probe_xy, int p0, int np,
     re = (float)(c * inv);
     im = (float)(s * inv);
   }
-  const size_t base = (grp * nblk + blk) * (size_t)(2 * group) * (kC16KB);
-  uint32_t* r0 = a16 + base + (size_t)(2 * g) * kC16KB;
-  uint32_t* r1 = r0 + kC16KB;
+  const size_t blk0 = (grp * nblk + blk) * (size_t)group;  // probe rows before this block's
   if constexpr (P == Prec::kF32) {
+    uint32_t* r0 = a16 + (blk0 + g) * (2 * kC16KB);
+    uint32_t* r1 = r0 + kC16KB;
     // row 2g: (Re a, -Im a), row 2g+1: (Im a, Re a) as float pairs
     r0[2 * bl] = __builtin_bit_cast(uint32_t, re);
     r0[2 * bl + 1] = __builtin_bit_cast(uint32_t, -im);
     r1[2 * bl] = __builtin_bit_cast(uint32_t, im);
     r1[2 * bl + 1] = __builtin_bit_cast(uint32_t, re);
   } else {
-    r0[bl] = pack16<P>(re, -im);
-    r1[bl] = pack16<P>(im, re);
+    a16[(blk0 + g) * kC16KB + bl] = pack16<P>(re, -im);
   }
 }
 
-// Workgroup shape per group size and operand form. Both shapes cover 128
-// union pixels. FP32 (bound by the matrix cores) gives each of 4 waves two
-// 16-pixel column tiles at two waves per SIMD; the 16-bit forms (bound by
-// operand fetch) give each of 8 waves one tile at four waves per SIMD, so
-// more waves cover each other's waits, for groups whose A block (2G rows of
-// 8 16-byte segments) has at least one segment per thread (G >= 32).
-template <int G, Prec P>
-struct C16Shape {
-  static constexpr bool kWide = P != Prec::kF32 && G >= 32;
-  static constexpr int NT = kWide ? 512 : 256;  // threads per workgroup
-  static constexpr int CT = kWide ? 1 : 2;      // 16-pixel column tiles per wave
-  static constexpr int WPE = kWide ? 4 : 2;     // waves per SIMD (register budget)
+// Four waves cover the 128 pixels of a union tile. FP32 (bound by the matrix
+// cores): each wave multiplies every probe row by two 16-pixel column tiles.
+// 16 bits (bound by operand reads from LDS): the waves form a grid of WM x WN,
+// each PT tiles of 16 probes by CT tiles of 16 pixels; a probe tile is one
+// operand read for two products per column (its real and its imaginary rows,
+// see C16), so a wave reads PT + CT operands for 2 PT CT products (G = 64: 6
+// for 16; eight waves of all 128 real-ified rows by one column read 9 for 8).
+constexpr int kNT16 = 256;
+template <int G>
+struct C16 {
+  static constexpr int WM = G == 64 ? 2 : 1, WN = 4 / WM;
+  static constexpr int PT = G / WM / 16, CT = 8 / WN;
 };
+constexpr int kCT32 = 2;
 constexpr int kTile16 = 128;  // union pixels per workgroup
 constexpr int kPitch16 = 36;             // uint32 per LDS row (32 + 4 pad)
 
+// What a workgroup sums: a list of items, each one union tile of 128 pixels
+// for the whole group, or (mode 1) one tile of one probe's own window.
 struct UnionGeom16 {
-  int y0, x0, uy, ux;
+  int y0, x0, uy, ux;  // union origin on the S-matrix, rows and columns
+  float rux;           // 1 / ux
+  // row of linear union pixel up: the float quotient is off by at most one
+  __device__ __forceinline__ int row(int up, int& col) const {
+    int a = (int)((float)up * rux);
+    col = up - a * ux;
+    if (col < 0) {
+      --a;
+      col += ux;
+    } else if (col >= ux) {
+      ++a;
+      col -= ux;
+    }
+    return a;
+  }
+};
+__device__ __forceinline__ UnionGeom16 union_geom(int y0, int x0, int uy, int ux) {
+  return UnionGeom16{y0, x0, uy, ux, 1.0f / (float)ux};
+}
+
+struct GroupWork {
+  const uint32_t* s16;   // packed S
+  const uint32_t* a16g;  // the group's A blocks
+  const int2* origin;    // the group's window origins
+  float2* window;        // the group's windows
+  int rowlen, ns, w, gcount, nblk;
+  float out_scale;
+  const int *offx, *offy, *zero;  // window offsets from the union origin (LDS)
+  UnionGeom16 U;                  // mode 0
+  int mode, first, stride, items;
+
+  __device__ __forceinline__ UnionGeom16 item(int k, int& tile, int& only) const {
+    if (mode == 0) {
+      tile = first + k * stride;
+      only = -1;
+      return U;
+    }
+    only = k % gcount;
+    tile = first + k / gcount * stride;
+    const int2 o = origin[only];
+    return union_geom(o.y, o.x, w, w);
+  }
 };
 
-template <int G, Prec P>
-__device__ __forceinline__ void contract16_tile(const uint32_t* __restrict__ s16, int rowlen,
-                                                const uint32_t* __restrict__ a16g, int np,
-                                                int p_base, int gcount, int ns, int w,
-                                                const UnionGeom16& U, int tile, const int* offx,
-                                                const int* offy, const int* rylo,
-                                                const int* ryhi, int only, float out_scale,
-                                                uint32_t* __restrict__ smem, uint32_t* buf0,
-                                                uint32_t* buf1, float2* __restrict__ window) {
-  constexpr int kNT16 = C16Shape<G, P>::NT, kCT16 = C16Shape<G, P>::CT;
-  static_assert(kNT16 / 64 * 16 * kCT16 == kTile16, "a workgroup covers one union tile");
-  static_assert(2 * G * 8 % kNT16 == 0 && kTile16 * 8 % kNT16 == 0,
-                "every thread stages whole 16-byte segments of A and B");
+// S pixels a thread stages for item k: tile columns (tid + 256 i) / 8. Columns
+// past the union read pixel 0 instead; their outputs are never stored, and a
+// B column only reaches its own output column, so nothing needs clearing.
+// Rows of absent probes and beams are zero in the packed A.
+template <int NBQ>
+__device__ __forceinline__ void tile_pixels(const GroupWork& wk, int k, int (&spix)[NBQ]) {
+  int tile, only;
+  const UnionGeom16 U = wk.item(k, tile, only);
+  const int npix = U.uy * U.ux, ns = wk.ns;
+#pragma unroll
+  for (int i = 0; i < NBQ; ++i) {
+    const int up = tile * kTile16 + (((int)threadIdx.x + kNT16 * i) >> 3);
+    int off = 0;
+    if (up < npix) {
+      int b;
+      int y = U.y0 + U.row(up, b), x = U.x0 + b;
+      // origins are below ns, unions at most 2 ns wide (W <= ns, spread <= ns)
+      y -= y >= 2 * ns ? 2 * ns : (y >= ns ? ns : 0);
+      x -= x >= 2 * ns ? 2 * ns : (x >= ns ? ns : 0);
+      off = y * ns + x;
+    }
+    spix[i] = off;
+  }
+}
+
+// FP32 sums of the workgroup's items.
+template <int G>
+__device__ __forceinline__ void contract32(const GroupWork& wk, const int* rylo, const int* ryhi,
+                                           uint32_t* buf0, uint32_t* buf1) {
   constexpr int RT = G / 8;
   constexpr int AROWS = 2 * G;
-  constexpr int ABUF = AROWS * kPitch16, BBUF = kTile16 * kPitch16;
+  static_assert(AROWS * 8 % kNT16 == 0 && kTile16 * 8 % kNT16 == 0,
+                "every thread stages whole 16-byte segments of A and B");
   constexpr int NAQ = AROWS * 8 / kNT16;     // u32x4 of the A block per thread
   constexpr int NBQ = kTile16 * 8 / kNT16;   // u32x4 of the B block per thread
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int npix = U.uy * U.ux;
-  const int nblk = rowlen / kC16KB;
-
-  // Row tiles (8 probes each) this wave multiplies: those holding a probe
-  // whose window meets a union row of the wave's 32 pixels. The skipped
-  // products only reach outputs the epilogue never stores, so the stored
-  // sums are the same. FP32 only: the 16-bit sums wait on operand fetch,
-  // and the branches cost them more than the skipped products save.
-  unsigned rmask = 0;
-  if constexpr (P != Prec::kF32) {
-    rmask = (1u << RT) - 1u;
-  } else if (only >= 0) {
-    rmask = 1u << (only / 8);
-  } else {
-    const int up0 = tile * kTile16 + 16 * kCT16 * wv;
-    if (up0 < npix) {
-      const int a0 = up0 / U.ux, a1 = (min(up0 + 16 * kCT16, npix) - 1) / U.ux;
-#pragma unroll
-      for (int r = 0; r < RT; ++r)
-        if (rylo[r] <= a1 && ryhi[r] >= a0) rmask |= 1u << r;
-    }
-  }
-
-  // S pixels this thread stages: tile column (tid + 256 i) / 8. Columns
-  // past the union read pixel 0 instead; their outputs are never stored,
-  // and a B column only reaches its own output column, so nothing needs
-  // clearing. Rows of absent probes and beams are zero in the packed A.
-  int spix[NBQ];
-#pragma unroll
-  for (int i = 0; i < NBQ; ++i) {
-    const int up = tile * kTile16 + ((tid + kNT16 * i) >> 3);
-    int off = 0;
-    if (up < npix) {
-      const int a = up / U.ux, b = up - a * U.ux;
-      off = ((U.y0 + a) % ns) * ns + ((U.x0 + b) % ns);
-    }
-    spix[i] = off;
-  }
-  const uint32_t* s16q = s16 + 4 * (tid & 7);
-
-  floatx4 acc[RT][kCT16];
-#pragma unroll
-  for (int r = 0; r < RT; ++r)
-#pragma unroll
-    for (int c = 0; c < kCT16; ++c) acc[r][c] = floatx4{0.f, 0.f, 0.f, 0.f};
   const int krow = lane >> 4, mcol = lane & 15;
 
-  if constexpr (P == Prec::kF32) {
-    // Operands go from global memory straight into LDS
-    // (global_load_lds_dwordx4: lane i of a wave's instruction writes its 16
-    // bytes at the wave's LDS base + 16 i), one K block ahead of the
-    // products, into two buffers that are separate LDS arrays (so the
-    // compiler sees that reads of one never wait for loads into the other);
-    // no registers stage them. An LDS row holds the 8 16-byte segments of
-    // one A row or of one pixel's K block, segment s stored at s ^ (row & 7),
-    // so the rows that one read instruction's lanes meet fall in different
-    // banks.
-    constexpr int P32 = kC16KB;  // LDS row: 32 words, no padding
-    constexpr int AOFF = 0, BOFF = AROWS * P32;
-    typedef __attribute__((address_space(3))) void* lds_ptr;
-    auto issue = [&](uint32_t* buf, int blk) {
-      const uint32_t* ab = a16g + (size_t)blk * AROWS * kC16KB;
+  // Operands go from global memory straight into LDS
+  // (global_load_lds_dwordx4: lane i of a wave's instruction writes its 16
+  // bytes at the wave's LDS base + 16 i), one K block ahead of the
+  // products, into two buffers that are separate LDS arrays (so the
+  // compiler sees that reads of one never wait for loads into the other);
+  // no registers stage them. An LDS row holds the 8 16-byte segments of
+  // one A row or of one pixel's K block, segment s stored at s ^ (row & 7),
+  // so the rows that one read instruction's lanes meet fall in different
+  // banks.
+  constexpr int P32 = kC16KB;  // LDS row: 32 words, no padding
+  constexpr int AOFF = 0, BOFF = AROWS * P32;
+  typedef __attribute__((address_space(3))) void* lds_ptr;
+  auto issue = [&](uint32_t* buf, int blk, const int (&spix)[NBQ]) {
+    const uint32_t* ab = wk.a16g + (size_t)blk * AROWS * kC16KB;
 #pragma unroll
-      for (int i = 0; i < NAQ; ++i) {
-        const int row = (tid + kNT16 * i) >> 3;
-        const int seg = (tid & 7) ^ (row & 7);
-        __builtin_amdgcn_global_load_lds(ab + (size_t)row * kC16KB + 4 * seg,
-                                         (lds_ptr)(buf + AOFF + 4 * (kNT16 * i + 64 * wv)), 16, 0,
-                                         0);
-      }
+    for (int i = 0; i < NAQ; ++i) {
+      const int row = (tid + kNT16 * i) >> 3;
+      const int seg = (tid & 7) ^ (row & 7);
+      __builtin_amdgcn_global_load_lds(ab + (size_t)row * kC16KB + 4 * seg,
+                                       (lds_ptr)(buf + AOFF + 4 * (kNT16 * i + 64 * wv)), 16, 0, 0);
+    }
 #pragma unroll
-      for (int i = 0; i < NBQ; ++i) {
-        const int row = (tid + kNT16 * i) >> 3;
-        const int seg = (tid & 7) ^ (row & 7);
-        __builtin_amdgcn_global_load_lds(s16 + (size_t)spix[i] * rowlen + blk * kC16KB + 4 * seg,
-                                         (lds_ptr)(buf + BOFF + 4 * (kNT16 * i + 64 * wv)), 16, 0,
-                                         0);
+    for (int i = 0; i < NBQ; ++i) {
+      const int row = (tid + kNT16 * i) >> 3;
+      const int seg = (tid & 7) ^ (row & 7);
+      __builtin_amdgcn_global_load_lds(
+          wk.s16 + (size_t)spix[i] * wk.rowlen + blk * kC16KB + 4 * seg,
+          (lds_ptr)(buf + BOFF + 4 * (kNT16 * i + 64 * wv)), 16, 0, 0);
+    }
+  };
+
+#pragma unroll 1
+  for (int k = 0; k < wk.items; ++k) {
+    int tile, only;
+    const UnionGeom16 U = wk.item(k, tile, only);
+    const int npix = U.uy * U.ux;
+    int spix[NBQ];
+    tile_pixels<NBQ>(wk, k, spix);
+
+    // Row tiles (8 probes each) this wave multiplies: those holding a probe
+    // whose window meets a union row of the wave's 32 pixels. The skipped
+    // products only reach outputs the epilogue never stores, so the stored
+    // sums are the same.
+    unsigned rmask = 0;
+    if (only >= 0) {
+      rmask = 1u << (only / 8);
+    } else {
+      const int up0 = tile * kTile16 + 16 * kCT32 * wv;
+      if (up0 < npix) {
+        int c;
+        const int a0 = U.row(up0, c), a1 = U.row(min(up0 + 16 * kCT32, npix) - 1, c);
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+          if (rylo[r] <= a1 && ryhi[r] >= a0) rmask |= 1u << r;
       }
-    };
+    }
+    rmask = __builtin_amdgcn_readfirstlane(rmask);
+
+    floatx4 acc[RT][kCT32];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int c = 0; c < kCT32; ++c) acc[r][c] = floatx4{0.f, 0.f, 0.f, 0.f};
     // both K steps' operands are read before the products, so the second
     // step's reads overlap the first step's products
     auto compute = [&](const uint32_t* buf) {
       const uint32_t* A = buf + AOFF + mcol * P32;
-      const uint32_t* Bm = buf + BOFF + (16 * kCT16 * wv + mcol) * P32;
-      u32x4 av[2][RT], bv[2][kCT16];
+      const uint32_t* Bm = buf + BOFF + (16 * kCT32 * wv + mcol) * P32;
+      u32x4 av[2][RT], bv[2][kCT32];
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         const int seg = 4 * ((krow + 4 * ks) ^ (mcol & 7));
@@ -361,7 +414,7 @@ __device__ __forceinline__ void contract16_tile(const uint32_t* __restrict__ s16
         for (int r = 0; r < RT; ++r)
           av[ks][r] = *reinterpret_cast<const u32x4*>(A + 16 * r * P32 + seg);
 #pragma unroll
-        for (int c = 0; c < kCT16; ++c)
+        for (int c = 0; c < kCT32; ++c)
           bv[ks][c] = *reinterpret_cast<const u32x4*>(Bm + 16 * c * P32 + seg);
       }
 #pragma unroll
@@ -370,101 +423,181 @@ __device__ __forceinline__ void contract16_tile(const uint32_t* __restrict__ s16
         for (int r = 0; r < RT; ++r)
           if (rmask >> r & 1u)
 #pragma unroll
-            for (int c = 0; c < kCT16; ++c) acc[r][c] = mfma16<P>(av[ks][r], bv[ks][c], acc[r][c]);
+            for (int c = 0; c < kCT32; ++c)
+              acc[r][c] = mfma16<Prec::kF32>(av[ks][r], bv[ks][c], acc[r][c]);
     };
-    // rows hold a whole number of K-block pairs: block 2j in buf0, 2j + 1
-    // in buf1
-    issue(buf0, 0);
+    // block 2j in buf0, 2j + 1 in buf1
+    issue(buf0, 0, spix);
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's loads are in LDS
     __syncthreads();
-    for (int blk = 0; blk < nblk; blk += 2) {
-      issue(buf1, blk + 1);
+    for (int blk = 0; blk < wk.nblk; blk += 2) {
+      const bool pair = blk + 1 < wk.nblk;
+      if (pair) issue(buf1, blk + 1, spix);
       compute(buf0);
       __builtin_amdgcn_s_waitcnt(0x0F70);
       // every wave's block blk + 1 is in LDS and no wave still reads buf0
       __syncthreads();
-      if (blk + 2 < nblk) issue(buf0, blk + 2);
+      if (!pair) break;
+      if (blk + 2 < wk.nblk) issue(buf0, blk + 2, spix);
       compute(buf1);
       __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();
     }
-  } else {
-    u32x4 ga[2][NAQ], gb[2][NBQ];
-    auto fetch = [&](int set, int blk) {
-      const u32x4* ab = reinterpret_cast<const u32x4*>(a16g + (size_t)blk * AROWS * kC16KB);
-#pragma unroll
-      for (int i = 0; i < NAQ; ++i) ga[set][i] = ab[tid + kNT16 * i];
-#pragma unroll
-      for (int i = 0; i < NBQ; ++i)
-        gb[set][i] =
-            *reinterpret_cast<const u32x4*>(s16q + (size_t)spix[i] * rowlen + blk * kC16KB);
-    };
-    auto stash = [&](int set) {
-      uint32_t* A = smem + set * ABUF;
-      uint32_t* Bm = smem + 2 * ABUF + set * BBUF;
-#pragma unroll
-      for (int i = 0; i < NAQ; ++i) {
-        const int idx = tid + kNT16 * i;
-        *reinterpret_cast<u32x4*>(A + (idx >> 3) * kPitch16 + 4 * (idx & 7)) = ga[set][i];
-      }
-#pragma unroll
-      for (int i = 0; i < NBQ; ++i) {
-        const int idx = tid + kNT16 * i;
-        *reinterpret_cast<u32x4*>(Bm + (idx >> 3) * kPitch16 + 4 * (idx & 7)) = gb[set][i];
-      }
-    };
-    auto compute = [&](int buf) {
-      const uint32_t* A = smem + buf * ABUF + mcol * kPitch16 + 4 * krow;
-      const uint32_t* Bm =
-          smem + 2 * ABUF + buf * BBUF + (16 * kCT16 * wv + mcol) * kPitch16 + 4 * krow;
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        u32x4 av[RT], bv[kCT16];
-#pragma unroll
-        for (int r = 0; r < RT; ++r)
-          av[r] = *reinterpret_cast<const u32x4*>(A + 16 * r * kPitch16 + 16 * ks);
-#pragma unroll
-        for (int c = 0; c < kCT16; ++c)
-          bv[c] = *reinterpret_cast<const u32x4*>(Bm + 16 * c * kPitch16 + 16 * ks);
-#pragma unroll
-        for (int r = 0; r < RT; ++r)
-#pragma unroll
-          for (int c = 0; c < kCT16; ++c) acc[r][c] = mfma16<P>(av[r], bv[c], acc[r][c]);
-      }
-    };
 
-    // rows hold a whole number of K-block pairs
-    fetch(0, 0);
-    fetch(1, 1);
-    for (int blk = 0; blk < nblk; blk += 2) {
-      stash(0);
-      __syncthreads();
-      fetch(0, min(blk + 2, nblk - 2));
-      compute(0);
-      stash(1);
-      __syncthreads();
-      fetch(1, min(blk + 3, nblk - 1));
-      compute(1);
+    const int w = wk.w;
+    const size_t w2 = (size_t)w * w;
+    const int* ox = only >= 0 ? wk.zero : wk.offx;
+    const int* oy = only >= 0 ? wk.zero : wk.offy;
+#pragma unroll
+    for (int c = 0; c < kCT32; ++c) {
+      const int up = tile * kTile16 + 16 * kCT32 * wv + 16 * c + mcol;
+      if (up >= npix) continue;
+      int b;
+      const int a = U.row(up, b);
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int g = 8 * r + 2 * krow + h;
+          if (g >= wk.gcount || (only >= 0 && g != only)) continue;
+          const int v = a - oy[g], u = b - ox[g];
+          if (v < 0 || v >= w || u < 0 || u >= w) continue;
+          wk.window[(size_t)g * w2 + (size_t)v * w + u] =
+              make_float2(acc[r][c][2 * h] * wk.out_scale, acc[r][c][2 * h + 1] * wk.out_scale);
+        }
+      }
     }
   }
-  __syncthreads();
+}
 
-  const size_t w2 = (size_t)w * w;
+// 16-bit sums of the workgroup's items. Probe tile r of a wave: the operand
+// read holds (Re, -Im) of 16 probes; swapping the halves of each word and
+// flipping the low one's sign gives (Im, Re), so the wave's two products are
+// the real and the imaginary parts of the sums. The next item's first two K
+// blocks are fetched during the last products of this one. Bound: the L2 /
+// Infinity Cache traffic and latency of the pixel rows.
+template <int G, Prec P>
+__device__ __forceinline__ void contract16(const GroupWork& wk, uint32_t* buf0, uint32_t* buf1) {
+  using C = C16<G>;
+  constexpr int PT = C::PT, CT = C::CT, P32 = kC16KB;
+  constexpr int AQ = G * 8;                         // 16-byte segments of the A block
+  constexpr int NAQ = (AQ + kNT16 - 1) / kNT16;     // of them per thread
+  constexpr int NBQ = kTile16 * 8 / kNT16;          // segments of the B block per thread
+  constexpr int BOFF = G * P32;
+  typedef __attribute__((address_space(3))) void* lds_ptr;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wv / C::WN, wn = wv % C::WN;
+  const int krow = lane >> 4, mcol = lane & 15;
+  const int seg = 4 * ((tid & 7) ^ ((tid >> 3) & 7));  // this thread's source segment (words)
+  const uint32_t* asrc = wk.a16g + (tid >> 3) * P32 + seg;
+  const size_t row = (size_t)wk.rowlen;
+
+  const uint32_t* bsrc[NBQ];
+  auto pixels = [&](int k) {
+    int spix[NBQ];
+    tile_pixels<NBQ>(wk, k, spix);
 #pragma unroll
-  for (int c = 0; c < kCT16; ++c) {
-    const int up = tile * kTile16 + 16 * kCT16 * wv + 16 * c + (lane & 15);
-    if (up >= npix) continue;
-    const int a = up / U.ux, b = up - a * U.ux;
+    for (int i = 0; i < NBQ; ++i) bsrc[i] = wk.s16 + spix[i] * row + seg;
+  };
+  // K block blk of the current item into buf; bsrc steps to the next block
+  auto issue = [&](uint32_t* buf, int blk) {
+    const uint32_t* ab = asrc + (size_t)blk * (G * P32);
 #pragma unroll
-    for (int r = 0; r < RT; ++r) {
+    for (int i = 0; i < NAQ; ++i)
+      if (AQ >= kNT16 || wv < AQ / 64)
+        __builtin_amdgcn_global_load_lds(ab + i * (kNT16 / 8) * P32,
+                                         (lds_ptr)(buf + 4 * (kNT16 * i + 64 * wv)), 16, 0, 0);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int g = 8 * r + 2 * (lane >> 4) + h;
-        if (g >= gcount || (only >= 0 && g != only)) continue;
-        const int v = a - offy[g], u = b - offx[g];
-        if (v < 0 || v >= w || u < 0 || u >= w) continue;
-        window[(size_t)(p_base + g) * w2 + (size_t)v * w + u] =
-            make_float2(acc[r][c][2 * h] * out_scale, acc[r][c][2 * h + 1] * out_scale);
+    for (int i = 0; i < NBQ; ++i) {
+      __builtin_amdgcn_global_load_lds(bsrc[i], (lds_ptr)(buf + BOFF + 4 * (kNT16 * i + 64 * wv)),
+                                       16, 0, 0);
+      bsrc[i] += P32;
+    }
+  };
+
+  pixels(0);
+  issue(buf0, 0);
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's loads are in LDS
+  __syncthreads();
+#pragma unroll 1
+  for (int k = 0; k < wk.items; ++k) {
+    floatx4 re[PT][CT], im[PT][CT];
+#pragma unroll
+    for (int r = 0; r < PT; ++r)
+#pragma unroll
+      for (int c = 0; c < CT; ++c) re[r][c] = im[r][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto compute = [&](const uint32_t* buf) {
+      const uint32_t* A = buf + (16 * PT * wm + mcol) * P32;
+      const uint32_t* Bm = buf + BOFF + (16 * CT * wn + mcol) * P32;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const int sg = 4 * ((krow + 4 * ks) ^ (mcol & 7));
+        u32x4 av[PT], bv[CT];
+#pragma unroll
+        for (int r = 0; r < PT; ++r)
+          av[r] = *reinterpret_cast<const u32x4*>(A + 16 * r * P32 + sg);
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+          bv[c] = *reinterpret_cast<const u32x4*>(Bm + 16 * c * P32 + sg);
+#pragma unroll
+        for (int r = 0; r < PT; ++r) {
+          u32x4 aw;
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            aw[q] = __builtin_amdgcn_alignbit(av[r][q], av[r][q], 16) ^ 0x8000u;
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {
+            re[r][c] = mfma16<P>(av[r], bv[c], re[r][c]);
+            im[r][c] = mfma16<P>(aw, bv[c], im[r][c]);
+          }
+        }
+      }
+    };
+#pragma unroll 1
+    for (int blk = 0; blk < wk.nblk; blk += 2) {
+      const bool pair = blk + 1 < wk.nblk;
+      if (pair) issue(buf1, blk + 1);
+      compute(buf0);
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      // every wave's block blk + 1 is in LDS and no wave still reads buf0
+      __syncthreads();
+      if (blk + 2 < wk.nblk) {
+        issue(buf0, blk + 2);
+      } else if (k + 1 < wk.items) {
+        pixels(k + 1);
+        issue(buf0, 0);
+      }
+      if (pair) compute(buf1);
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      __syncthreads();
+    }
+
+    int tile, only;
+    const UnionGeom16 U = wk.item(k, tile, only);
+    const int npix = U.uy * U.ux;
+    const unsigned w = (unsigned)wk.w;
+    int ca[CT], cb[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      const int up = tile * kTile16 + 16 * CT * wn + 16 * c + mcol;
+      ca[c] = U.row(up, cb[c]);
+      if (up >= npix) ca[c] = -(1 << 20);  // outside every window
+    }
+#pragma unroll
+    for (int r = 0; r < PT; ++r) {
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        const int g = 16 * (PT * wm + r) + 4 * krow + h;
+        if (g >= wk.gcount || (only >= 0 && g != only)) continue;
+        const int oy = only >= 0 ? 0 : wk.offy[g], ox = only >= 0 ? 0 : wk.offx[g];
+        float2* win = wk.window + (size_t)g * w * w;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          const unsigned v = (unsigned)(ca[c] - oy), u = (unsigned)(cb[c] - ox);
+          if (v < w && u < w)
+            win[v * w + u] = make_float2(re[r][c][h] * wk.out_scale, im[r][c][h] * wk.out_scale);
+        }
       }
     }
   }
@@ -473,32 +606,40 @@ __device__ __forceinline__ void contract16_tile(const uint32_t* __restrict__ s16
 // Grid: x walks the union tiles of a group, y the probe groups of every
 // segment (segment k owns groups g_begin .. g_begin + ceil(np / G)).
 template <int G, Prec P>
-__global__ __launch_bounds__((C16Shape<G, P>::NT))
-__attribute__((amdgpu_waves_per_eu(C16Shape<G, P>::WPE))) void k_contract16(
-    const ContractSegs segs, int w) {
-  // 16-bit operands: one array for both register-staged buffers; FP32: two
-  // arrays, one per buffer (A block, then B block)
+__global__ __launch_bounds__(kNT16)
+__attribute__((amdgpu_waves_per_eu(P == Prec::kF32 ? 2 : 3))) void k_contract16(
+    const ContractSegs segs, int w, int slots, int set) {
+  // two arrays, one per buffer (A block, then B block)
   constexpr bool F32 = P == Prec::kF32;
-  constexpr int LDS = F32 ? 1 : 2 * (2 * G * kPitch16) + 2 * (kTile16 * kPitch16);
-  constexpr int LDSB = F32 ? (2 * G + kTile16) * kC16KB : 1;
-  __shared__ uint32_t smem[LDS];
+  constexpr int LDSB = ((F32 ? 2 : 1) * G + kTile16) * kC16KB;
   __shared__ uint32_t sbuf0[LDSB], sbuf1[LDSB];
   __shared__ int offx[G], offy[G];
   __shared__ int zero[G];
   __shared__ int ginfo[6];
   __shared__ int rylo[G / 8], ryhi[G / 8];  // union rows each row tile's windows span
   const int tid = threadIdx.x;
+  // which group, and which of its slots
+  int gidx, slot;
+  if (set == 0) {
+    gidx = blockIdx.x / slots;
+    slot = blockIdx.x % slots;
+  } else {
+    const int i = blockIdx.x >> 3, per = set * slots;
+    gidx = ((i / per) * 8 + (blockIdx.x & 7)) * set + i % set;
+    slot = i % per / set;
+    if (gidx >= segs.groups) return;
+  }
   int k = 0;  // segment of this group (uniform)
-  while (k + 1 < segs.n && (int)blockIdx.y >= segs.s[k + 1].g_begin) ++k;
+  while (k + 1 < segs.n && gidx >= segs.s[k + 1].g_begin) ++k;
   const ContractSeg& sg = segs.s[k];
   const uint32_t* __restrict__ s16 = sg.s16;
   const int2* __restrict__ origin = sg.origin;
   const int rowlen = sg.rowlen, ns = sg.ns, np = sg.np;
-  const int grp = (int)blockIdx.y - sg.g_begin;
+  const int grp = gidx - sg.g_begin;
   const int p_base = grp * G;
   const int gcount = min(G, np - p_base);
   const int nblk = rowlen / kC16KB;
-  const uint32_t* a16g = sg.a16 + (size_t)grp * nblk * (2 * G) * kC16KB;
+  const uint32_t* a16g = sg.a16 + (size_t)grp * nblk * ((F32 ? 2 : 1) * G) * kC16KB;
   if (tid < 64) {
     // group geometry in wave 0, one lane per probe (G <= 64): offsets of
     // each window from the first, their extent, and the union origin
@@ -506,8 +647,8 @@ __attribute__((amdgpu_waves_per_eu(C16Shape<G, P>::WPE))) void k_contract16(
     int rx = 0, ry = 0;
     if (tid < gcount) {
       const int2 o = origin[p_base + tid];
-      rx = wrap_mod16((long long)o.x - o0.x + ns / 2, ns) - ns / 2;
-      ry = wrap_mod16((long long)o.y - o0.y + ns / 2, ns) - ns / 2;
+      rx = wrap_near(o.x - o0.x, ns);
+      ry = wrap_near(o.y - o0.y, ns);
     }
     int minx = rx, maxx = rx, miny = ry, maxy = ry;
 #pragma unroll
@@ -527,13 +668,13 @@ __attribute__((amdgpu_waves_per_eu(C16Shape<G, P>::WPE))) void k_contract16(
       // output pixel gets the same sum either way)
       const long long uni = (long long)(w + maxx - minx) * (w + maxy - miny);
       ginfo[0] = uni <= (long long)gcount * w * w ? 0 : 1;
-      ginfo[1] = wrap_mod16((long long)o0.y + miny, ns);
-      ginfo[2] = wrap_mod16((long long)o0.x + minx, ns);
+      ginfo[1] = o0.y + miny < 0 ? o0.y + miny + ns : o0.y + miny;  // minx, miny in [-ns/2, 0]
+      ginfo[2] = o0.x + minx < 0 ? o0.x + minx + ns : o0.x + minx;
       ginfo[3] = w + (maxy - miny);
       ginfo[4] = w + (maxx - minx);
     }
   }
-  for (int g = tid; g < G; g += C16Shape<G, P>::NT) zero[g] = 0;
+  for (int g = tid; g < G; g += kNT16) zero[g] = 0;
   __syncthreads();
   if (tid < G / 8) {
     int lo = 1 << 30, hi = -1;
@@ -549,21 +690,33 @@ __attribute__((amdgpu_waves_per_eu(C16Shape<G, P>::WPE))) void k_contract16(
   }
   __syncthreads();
   // the workgroups of a group share its tiles round-robin
-  if (ginfo[0] == 0) {
-    const UnionGeom16 U{ginfo[1], ginfo[2], ginfo[3], ginfo[4]};
-    for (int tile = blockIdx.x; tile * kTile16 < U.uy * U.ux; tile += gridDim.x)
-      contract16_tile<G, P>(s16, rowlen, a16g, np, p_base, gcount, ns, w, U, tile, offx, offy,
-                            rylo, ryhi, -1, sg.out_scale, smem, sbuf0, sbuf1, sg.window);
-  } else {
-    for (int tile = blockIdx.x; tile * kTile16 < w * w; tile += gridDim.x) {
-      for (int g = 0; g < gcount; ++g) {
-        const int2 o = origin[p_base + g];
-        const UnionGeom16 U{o.y, o.x, w, w};
-        contract16_tile<G, P>(s16, rowlen, a16g, np, p_base, gcount, ns, w, U, tile, zero, zero,
-                              rylo, ryhi, g, sg.out_scale, smem, sbuf0, sbuf1, sg.window);
-      }
-    }
-  }
+  GroupWork wk;
+  wk.s16 = s16;
+  wk.a16g = a16g;
+  wk.origin = origin + p_base;
+  wk.window = sg.window + (size_t)p_base * w * w;
+  wk.rowlen = rowlen;
+  wk.ns = ns;
+  wk.w = w;
+  wk.gcount = gcount;
+  wk.nblk = nblk;
+  wk.out_scale = sg.out_scale;
+  wk.offx = offx;
+  wk.offy = offy;
+  wk.zero = zero;
+  wk.mode = __builtin_amdgcn_readfirstlane(ginfo[0]);
+  wk.U = union_geom(__builtin_amdgcn_readfirstlane(ginfo[1]),
+                    __builtin_amdgcn_readfirstlane(ginfo[2]),
+                    __builtin_amdgcn_readfirstlane(ginfo[3]),
+                    __builtin_amdgcn_readfirstlane(ginfo[4]));
+  wk.first = slot;
+  wk.stride = slots;
+  const int tiles = ((wk.mode == 0 ? wk.U.uy * wk.U.ux : w * w) + kTile16 - 1) / kTile16;
+  const int mine = (tiles - wk.first + wk.stride - 1) / wk.stride;
+  wk.items = mine * (wk.mode == 0 ? 1 : gcount);
+  if (wk.first >= tiles) return;
+  if constexpr (F32) contract32<G>(wk, rylo, ryhi, sbuf0, sbuf1);
+  else contract16<G, P>(wk, sbuf0, sbuf1);
 }
 
 inline unsigned blocks16(size_t n, unsigned bs) { return (unsigned)((n + bs - 1) / bs); }
@@ -619,9 +772,13 @@ hipError_t launch_alpha16(const double* probe_xy, int p0, int np, const ActiveBe
 hipError_t launch_contract16(const ContractSegs& segs, int w, int group, Prec prec,
                              int window_tile_div, hipStream_t st) {
   if (segs.n < 1 || segs.n > kMaxSeg || segs.groups < 1) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)contract_tile_slots(w, window_tile_div), (unsigned)segs.groups);
+  const int slots = contract_tile_slots(w, window_tile_div, segs.groups);
+  int set = segs.groups >= 128 ? 4 : 0;
+  const int wgs = set == 0 ? slots * segs.groups
+                           : ((segs.groups + set - 1) / set + 7) / 8 * 8 * set * slots;
+  const dim3 grid((unsigned)wgs);
 #define C16(GG, PP) \
-  hipLaunchKernelGGL((k_contract16<GG, PP>), grid, dim3(C16Shape<GG, PP>::NT), 0, st, segs, w)
+  hipLaunchKernelGGL((k_contract16<GG, PP>), grid, dim3(kNT16), 0, st, segs, w, slots, set)
 #define C16G(PP)                          \
   switch (group) {                        \
     case 16: C16(16, PP); break;          \

@@ -20,6 +20,12 @@ namespace {
 // per group for W >= 128, and the union tiles of 128 pixels.
 constexpr int kCG128 = 64;
 constexpr int kCTile = 128;
+// Workgroups a window-sum launch has at least: four rounds of the 512 that are
+// resident, so that groups of unequal unions even out. With the tuned slots
+// alone, one group of 15 probes (W = 128) ran on 16 workgroups (199 us, now
+// 30) and 89 ragged groups (W = 64) on 356 (787 us, now 386). More than the
+// tiles of two windows per group are never needed by windows that overlap.
+constexpr int kCSlots = 2048;
 
 // ---------------------------------------------------------------------------
 // W = 256 windows (too large for one workgroup's LDS): the 2D FFT runs as
@@ -341,9 +347,10 @@ inline unsigned blocks_for(size_t n, unsigned bs) { return (unsigned)((n + bs - 
 
 int contract_group(int w) { return w >= 128 ? kCG128 : (w >= 64 ? 32 : 16); }
 
-int contract_tile_slots(int w, int window_tile_div) {
+int contract_tile_slots(int w, int window_tile_div, int groups) {
   const int own = (w * w + kCTile - 1) / kCTile;  // tiles of one window
-  return std::max(1, own / std::max(1, window_tile_div));
+  const int want = std::max(1, own / std::max(1, window_tile_div));
+  return std::max(want, std::min(2 * own, (kCSlots + groups - 1) / groups));
 }
 
 int window_big_tiles(int w) { return w / 16; }
