@@ -164,9 +164,9 @@ int prism_probe_order(const prism_plan* plan, int f, const double* probe_xy_host
 /* Select the operand precision of prism_probe_outputs for this plan
  * (PRISM_PREC_*; PRISM_EINVAL otherwise). With BF16/FP16 each call first
  * packs the active beams of the S-matrix into a pixel-major 16-bit copy in
- * the workspace (each beam scaled by an exact power of two so that its
- * largest component is below 1, the coefficient divided by the same factor)
- * and runs the window sum on 16-bit matrix cores with FP32 accumulation;
+ * the workspace (FP16: each beam scaled by an exact power of two so that its
+ * largest component is below 1, the coefficient divided by the same factor;
+ * BF16 has FP32's range and takes the values as they are) and runs the window sum on 16-bit matrix cores with FP32 accumulation;
  * everything after the window sum stays FP32/FP64. The workspace sizes
  * returned by prism_probe_workspace_bytes follow the plan's precision, so
  * query them after this call. Setting the precision is not stream-ordered:
@@ -246,7 +246,7 @@ int prism_probe_outputs(prism_plan* plan, int f, double alpha_max_mrad, const vo
  * Limit: PRISM_ENOSPACE, before anything is enqueued, when the probe step's
  * minimum workspace (prism_probe_workspace_bytes) exceeds the array, e.g.
  * 305 active beams on a 512^2 S-matrix (649 MiB in FP32, 329 MiB in BF16);
- * 69 active beams at 512^2 need 193 MiB. Other errors as
+ * 69 active beams at 512^2 need 163 MiB. Other errors as
  * prism_probe_outputs.
  * Every call on one GPU shares that GPU's array, and it keeps the last
  * call's contents: calls that overlap on one GPU (other streams, other host
@@ -497,7 +497,8 @@ int prism_server_call_stats(const prism_server* server, long long* probe_calls,
  *     W >= 128, 32 for W >= 64, else 16), which also sets the tile shape
  *     prism_probe_group reports;
  *   window_tile_div: window-sum workgroups per probe group are the 128-pixel
- *     tiles of one window divided by this (1 .. 64; 4).
+ *     tiles of one window divided by this (1 .. 64; 4), or more where a launch
+ *     has too few groups to fill the GPU with them.
  * Query workspace sizes after setting it. PRISM_EINVAL for values outside
  * these ranges (nothing is changed then). */
 typedef struct {

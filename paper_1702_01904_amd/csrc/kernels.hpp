@@ -131,15 +131,20 @@ enum class Prec { kBF16 = 1, kFP16 = 2, kF32 = 3 };
 constexpr int kC16KB = 32;  // 32-bit words per K block row
 __host__ __device__ constexpr int prec_block_beams(Prec p) { return p == Prec::kF32 ? 16 : 32; }
 __host__ __device__ constexpr int prec_words(Prec p) { return p == Prec::kF32 ? 2 : 1; }
+// FP16 operands carry a power-of-two scale per beam.
+__host__ __device__ constexpr bool prec_scaled(Prec p) { return p == Prec::kFP16; }
 // scale[a] = 2^-e with e the smallest integer such that every |Re|, |Im| of
 // active beam a's plane is < 2^e (1 for an all-zero plane); partial holds
 // n_act * kScaleSplit floats of per-block maxima (ns >= 64).
 constexpr int kScaleSplit = 32;
 hipError_t launch_s16_scale(const float2* smatrix, const ActiveBeam* act, int n_act, int ns,
                             float* partial, float* scale, hipStream_t st);
-// s16 [ns*ns][n_actp][2] 16-bit: (Re, Im) of scale[a] * S_a(pixel); zero for a >= n_act.
+// s16 [ns*ns][n_actp][2]: (Re, Im) of S_a(pixel) in the operand form (FP16:
+// times scale[a]); zero for a >= n_act. org != nullptr: only the 64-pixel
+// tiles that one of the np windows of side w at these origins meets.
 hipError_t launch_s16_pack(const float2* smatrix, const ActiveBeam* act, int n_act, int n_actp,
-                           int ns, const float* scale, void* s16, Prec prec, hipStream_t st);
+                           int ns, const float* scale, const int2* org, int np, int w, void* s16,
+                           Prec prec, hipStream_t st);
 // a16: per probe group and K block, the A block of alpha'' = exp(i phase)
 // (FP16: / scale[a]) (16 bits: [G][32 beams] words (Re, -Im); FP32: real-ified [2G][32
 // words]); also the window origins.

@@ -339,6 +339,7 @@ const prism_plan::PixLists* get_pixlists(prism_plan* p, int w, int f, const pris
 // ---------------------------------------------------------------- layouts
 
 constexpr size_t kChunkBytes = size_t(1) << 30;  // preferred probe-window bytes per chunk
+constexpr int kSelectProbes = 2048;  // most probes of a fill that packs only what its windows meet
 
 size_t state_bytes(int n) { return (size_t)n * (n / 2) * sizeof(float2); }
 
@@ -409,8 +410,8 @@ struct PackShape {
 };
 struct PackWs {
   prism::ActiveBeam* act;
-  float* scale;       // 16-bit: [n_act] power-of-two beam scales
-  float* scale_part;  // 16-bit: [n_act][kScaleSplit] per-block maxima
+  float* scale;       // FP16: [n_act] power-of-two beam scales
+  float* scale_part;  // FP16: [n_act][kScaleSplit] per-block maxima
   uint32_t* s16;      // packed S: [ns^2][n_actp] (re, im), one word (16-bit) or two (FP32)
 };
 struct ProbeBatchWs {
@@ -434,9 +435,9 @@ size_t probe_batch_layout(int w, int G, prism::Prec pk, const std::vector<PackSh
     const PackShape& ps = packs[k];
     PackWs& pw = bw->packs[k];
     pw.act = c.take<prism::ActiveBeam>(ps.n_act);
-    pw.scale = pk == prism::Prec::kF32 ? nullptr : c.take<float>(ps.n_act);
-    pw.scale_part =
-        pk == prism::Prec::kF32 ? nullptr : c.take<float>((size_t)ps.n_act * prism::kScaleSplit);
+    const bool scaled = prism::prec_scaled(pk);
+    pw.scale = scaled ? c.take<float>(ps.n_act) : nullptr;
+    pw.scale_part = scaled ? c.take<float>((size_t)ps.n_act * prism::kScaleSplit) : nullptr;
     pw.s16 = c.take<uint32_t>((size_t)ps.ns * ps.ns * ps.n_actp * prism::prec_words(pk));
     nblk_max = std::max(nblk_max, ps.n_actp / prism::prec_block_beams(pk));
   }
@@ -678,12 +679,36 @@ int run_sub(std::vector<Req>& rq, const Sub& sb, int chunk, void* base, hipStrea
     HIP_TRY(hipMemcpyAsync(pw.act, r.act->data(), r.act->size() * sizeof(prism::ActiveBeam),
                            hipMemcpyHostToDevice, st),
             "copy active beams");
-    if (!f32)
+    if (prism::prec_scaled(pr))
       LAUNCH(r.p, st, "s16_scale",
              prism::launch_s16_scale(r.S, pw.act, r.n_act, r.ns, pw.scale_part, pw.scale, st));
-    LAUNCH(r.p, st, f32 ? "s32_pack" : "s16_pack",
-           prism::launch_s16_pack(r.S, pw.act, r.n_act, r.n_actp, r.ns, pw.scale, pw.s16, pr, st));
   }
+  // The S-matrices are packed at the first flush, after its coefficient
+  // launches: those give the window origins, and where the flush holds every
+  // probe of this fill and they are few (kSelectProbes), only the pixel tiles
+  // that a window meets are packed. Each tile's workgroups test every window,
+  // 256 at a time, so the test stays below the copy it may save: with 15
+  // probes of 128^2 windows on a 512^2 S-matrix (305 beams) the pack takes
+  // 53 us instead of 300, with 1024 scattered 256^2 windows on 1024^2
+  // (289 beams, BF16) 700 instead of 990.
+  bool packed = false;
+  auto pack_all = [&](int probes) -> int {
+    packed = true;
+    const bool select = probes == sb.probes && probes <= kSelectProbes;
+    for (size_t k = 0; k < sb.packs.size(); ++k) {
+      const Req& r = rq[sb.packs[k]];
+      const PackWs& pw = bw.packs[k];
+      // origins lie in [0, ns) of their own S-matrix: with several sizes in
+      // one fill everything is packed
+      bool same_ns = true;
+      for (int i : sb.reqs) same_ns = same_ns && rq[i].ns == r.ns;
+      LAUNCH(r.p, st, f32 ? "s32_pack" : "s16_pack",
+             prism::launch_s16_pack(r.S, pw.act, r.n_act, r.n_actp, r.ns, pw.scale,
+                                    select && same_ns ? bw.origin : nullptr, probes, w, pw.s16, pr,
+                                    st));
+    }
+    return PRISM_OK;
+  };
   std::vector<Piece> pc;
   int used = 0;
   auto flush = [&]() -> int {
@@ -707,6 +732,8 @@ int run_sub(std::vector<Req>& rq, const Sub& sb, int chunk, void* base, hipStrea
       a16_off += (size_t)ngrp * nblk * 2 * G * prism::kC16KB;
     }
     cs.groups = g;
+    if (!packed)
+      if (int e = pack_all(used)) return e;
     LAUNCH(lp, st, f32 ? "contract" : "contract16",
            prism::launch_contract16(cs, w, G, pr, r0.tile_div, st));
     // window FFT, |Psi|^2 and detector sums (or the CBED)

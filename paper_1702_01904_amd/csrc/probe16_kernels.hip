@@ -3,13 +3,16 @@
 // FP16) operands for callers that accept their rounding, or with FP32
 // operands. Accumulation is FP32 in both.
 //
-//  * Every active beam plane S_a is multiplied by an exact power of two
+//  * FP16: every active beam plane S_a is multiplied by an exact power of two
 //    scale[a] that brings its largest component below 1, and alpha_a is
 //    divided by the same factor, so the product is unchanged in exact
-//    arithmetic and FP16 stays in range.
-//  * S is packed once per call into a pixel-major 16-bit copy
-//    s16[pixel][beam] = (Re, Im), beam rows padded to whole K blocks, so that
-//    one 32-beam K block of a pixel is 128 contiguous bytes.
+//    arithmetic and FP16 stays in range. BF16 has FP32's range: a power of
+//    two only shifts the operands' exponents there, every product is the
+//    same, and the pass over S that finds the scales is left out.
+//  * S is packed once per call into a pixel-major copy s16[pixel][beam] =
+//    (Re, Im), beam rows padded to whole K blocks, so that one 32-beam K
+//    block of a pixel is 128 contiguous bytes. Calls of few probes pack only
+//    the pixel tiles that some window meets.
 //  * alpha is written by k_alpha16 directly in the MFMA A layout per probe
 //    group and K block: FP32 real-ified (rows 2g: (Re, -Im), rows 2g+1: (Im,
 //    Re)); 16-bit one row (Re, -Im) per probe, from which the matrix core's
@@ -123,29 +126,64 @@ __global__ __launch_bounds__(256) void k_s16_scale(const float* __restrict__ par
   scale[a] = sc;
 }
 
+// Whether some window (of side w, origins org[0 .. np) in [0, ns)) holds a
+// pixel of the 64 from pix0 on (one answer per workgroup of 256 threads).
+__device__ __forceinline__ bool tile_met(const int2* __restrict__ org, int np, int w, int ns,
+                                         int pix0) {
+  const int y0 = pix0 / ns, x0 = pix0 - y0 * ns;
+  const int len = min(64, ns - x0);  // pixels in row y0; the rest (ns not a multiple of 64) below
+  bool met = false;
+  for (int p = threadIdx.x; p < np; p += 256) {
+    const int2 o = org[p];
+    // row y meets when y - o.y (wrapped) is in [0, w); pixels [x, x + n) of
+    // a row meet when x - o.x (wrapped) is in [0, w) or o.x is among them
+    auto hit = [&](int y, int x, int n) {
+      const int dy = y - o.y + (y < o.y ? ns : 0), dx = x - o.x + (x < o.x ? ns : 0);
+      return dy < w && (dx < w || dx + n > ns);
+    };
+    met = met || hit(y0, x0, len);
+    for (int y = y0 + 1, left = 64 - len; left > 0; ++y, left -= ns)  // ns = 48, 96, ...
+      met = met || (y < ns && hit(y, 0, min(left, ns)));
+  }
+  return __syncthreads_or(met) != 0;
+}
+
 // FP32: 16 beams x 64 pixels per workgroup, transposed through LDS; a pixel
-// row holds n_actp (re, im) float pairs, zero past the active beams.
+// row holds n_actp (re, im) float pairs, zero past the active beams. org !=
+// nullptr: only the pixel tiles that one of np windows meets (the window sum
+// multiplies other pixels too, but stores none of those sums). blockIdx.y
+// walks the beam blocks.
 __global__ __launch_bounds__(256) void k_s32_pack(const float2* __restrict__ S,
                                                   const ActiveBeam* __restrict__ act, int n_act,
-                                                  int n_actp, int ns, float2* __restrict__ s32) {
+                                                  int n_actp, int ns, const int2* __restrict__ org,
+                                                  int np, int w, float2* __restrict__ s32) {
   __shared__ float2 tile[64][17];
   const int tid = threadIdx.x;
   const size_t pix0 = (size_t)blockIdx.x * 64;
-  const int a0 = blockIdx.y * 16;
+  if (org && !tile_met(org, np, w, ns, (int)pix0)) return;
   const size_t npix = (size_t)ns * ns;
+  float2 v[4];
+  auto load = [&](int a0) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int idx = tid + 256 * i;
-    const int j = idx / 64, px = idx % 64;
-    const int a = a0 + j;
-    tile[px][j] = a < n_act ? S[(size_t)act[a].plane * npix + pix0 + px] : make_float2(0.f, 0.f);
-  }
-  __syncthreads();
+    for (int i = 0; i < 4; ++i) {
+      const int a = a0 + (tid + 256 * i) / 64, px = tid % 64;
+      v[i] = a < n_act ? S[(size_t)act[a].plane * npix + pix0 + px] : make_float2(0.f, 0.f);
+    }
+  };
+  const int step = 16 * gridDim.y;
+  load(blockIdx.y * 16);
+  for (int a0 = blockIdx.y * 16; a0 < n_actp; a0 += step) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int idx = tid + 256 * i;
-    const int px = idx / 16, j = idx % 16;
-    s32[(pix0 + px) * n_actp + a0 + j] = tile[px][j];
+    for (int i = 0; i < 4; ++i) tile[tid % 64][(tid + 256 * i) / 64] = v[i];
+    __syncthreads();
+    if (a0 + step < n_actp) load(a0 + step);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int idx = tid + 256 * i;
+      const int px = idx / 16, j = idx % 16;
+      s32[(pix0 + px) * n_actp + a0 + j] = tile[px][j];
+    }
+    __syncthreads();
   }
 }
 
@@ -154,31 +192,40 @@ template <Prec P>
 __global__ __launch_bounds__(256) void k_s16_pack(const float2* __restrict__ S,
                                                   const ActiveBeam* __restrict__ act, int n_act,
                                                   int n_actp, int ns, const float* __restrict__ scale,
+                                                  const int2* __restrict__ org, int np, int w,
                                                   uint32_t* __restrict__ s16) {
   __shared__ uint32_t tile[64][33];
   const int tid = threadIdx.x;
   const size_t pix0 = (size_t)blockIdx.x * 64;
-  const int a0 = blockIdx.y * 32;
+  if (org && !tile_met(org, np, w, ns, (int)pix0)) return;
   const size_t npix = (size_t)ns * ns;
+  uint32_t v[8];
+  auto load = [&](int a0) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int idx = tid + 256 * i;
-    const int j = idx / 64, px = idx % 64;
-    const int a = a0 + j;
-    uint32_t v = 0u;
-    if (a < n_act) {
-      const float2 z = S[(size_t)act[a].plane * npix + pix0 + px];
-      const float sc = scale[a];
-      v = pack16<P>(z.x * sc, z.y * sc);
+    for (int i = 0; i < 8; ++i) {
+      const int a = a0 + (tid + 256 * i) / 64, px = tid % 64;
+      v[i] = 0u;
+      if (a < n_act) {
+        const float2 z = S[(size_t)act[a].plane * npix + pix0 + px];
+        const float sc = prec_scaled(P) ? scale[a] : 1.f;
+        v[i] = pack16<P>(z.x * sc, z.y * sc);
+      }
     }
-    tile[px][j] = v;
-  }
-  __syncthreads();
+  };
+  const int step = 32 * gridDim.y;
+  load(blockIdx.y * 32);
+  for (int a0 = blockIdx.y * 32; a0 < n_actp; a0 += step) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int idx = tid + 256 * i;
-    const int px = idx / 32, j = idx % 32;
-    s16[(pix0 + px) * n_actp + a0 + j] = tile[px][j];
+    for (int i = 0; i < 8; ++i) tile[tid % 64][(tid + 256 * i) / 64] = v[i];
+    __syncthreads();
+    if (a0 + step < n_actp) load(a0 + step);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int idx = tid + 256 * i;
+      const int px = idx / 32, j = idx % 32;
+      s16[(pix0 + px) * n_actp + a0 + j] = tile[px][j];
+    }
+    __syncthreads();
   }
 }
 
@@ -217,7 +264,7 @@ __global__ void k_alpha16(const double* __restrict__ probe_xy, int p0, int np,
     t -= floor(t);
     double s, c;
     sincospi(2.0 * t, &s, &c);
-    const double inv = P == Prec::kF32 ? 1.0 : 1.0 / (double)scale[a];
+    const double inv = prec_scaled(P) ? 1.0 / (double)scale[a] : 1.0;
     re = (float)(c * inv);
     im = (float)(s * inv);
   }
@@ -735,17 +782,21 @@ hipError_t launch_s16_scale(const float2* smatrix, const ActiveBeam* act, int n_
 }
 
 hipError_t launch_s16_pack(const float2* smatrix, const ActiveBeam* act, int n_act, int n_actp,
-                           int ns, const float* scale, void* s16, Prec prec, hipStream_t st) {
-  const unsigned gx = (unsigned)((size_t)ns * ns / 64);
+                           int ns, const float* scale, const int2* org, int np, int w, void* s16,
+                           Prec prec, hipStream_t st) {
+  const int nblk = n_actp / prec_block_beams(prec);
+  // the workgroups of a tile that packs selectively repeat its window test:
+  // a quarter as many, each walking up to four beam blocks
+  const dim3 grid((unsigned)((size_t)ns * ns / 64), (unsigned)(org ? (nblk + 3) / 4 : nblk));
   if (prec == Prec::kF32) {
-    hipLaunchKernelGGL(k_s32_pack, dim3(gx, (unsigned)(n_actp / 16)), dim3(256), 0, st, smatrix,
-                       act, n_act, n_actp, ns, static_cast<float2*>(s16));
+    hipLaunchKernelGGL(k_s32_pack, grid, dim3(256), 0, st, smatrix, act, n_act, n_actp, ns, org,
+                       np, w, static_cast<float2*>(s16));
   } else if (prec == Prec::kBF16) {
-    hipLaunchKernelGGL(k_s16_pack<Prec::kBF16>, dim3(gx, (unsigned)(n_actp / 32)), dim3(256), 0,
-                       st, smatrix, act, n_act, n_actp, ns, scale, static_cast<uint32_t*>(s16));
+    hipLaunchKernelGGL(k_s16_pack<Prec::kBF16>, grid, dim3(256), 0, st, smatrix, act, n_act,
+                       n_actp, ns, scale, org, np, w, static_cast<uint32_t*>(s16));
   } else {
-    hipLaunchKernelGGL(k_s16_pack<Prec::kFP16>, dim3(gx, (unsigned)(n_actp / 32)), dim3(256), 0,
-                       st, smatrix, act, n_act, n_actp, ns, scale, static_cast<uint32_t*>(s16));
+    hipLaunchKernelGGL(k_s16_pack<Prec::kFP16>, grid, dim3(256), 0, st, smatrix, act, n_act,
+                       n_actp, ns, scale, org, np, w, static_cast<uint32_t*>(s16));
   }
   return hipGetLastError();
 }
