@@ -213,82 +213,336 @@ __global__ __launch_bounds__(kBigNT) void k_window_cols_lds(const float2* __rest
 }
 
 // ---------------------------------------------------------------------------
-#ifndef PRISM_WD_GRID
-#define PRISM_WD_GRID 1048576  // window kernel: most workgroups (each then walks probes)
-#endif
-#ifndef PRISM_WD128_NT
-#define PRISM_WD128_NT 1024  // threads per W = 128 window workgroup
-#endif
 constexpr int kWdChunks = 16;  // bin-list chunks whose pixel indices load together
 
 // Threads per window workgroup: W^2 / 16 rounded up to whole waves.
 __host__ __device__ constexpr int wd_nt(int w) {
-  return w == 128 ? PRISM_WD128_NT : ((w * w / 16) < 64 ? 64 : (w * w / 16 + 63) / 64 * 64);
+  return w * w / 16 < 64 ? 64 : (w * w / 16 + 63) / 64 * 64;
+}
+// Waves per SIMD the registers are limited for: at W = 128 two workgroups of
+// 16 waves (64 registers).
+__host__ __device__ constexpr int wd_wpe(int w) { return w == 128 ? 8 : 6; }
+
+// The window transforms keep the window in registers and pass it from stage
+// to stage through LDS one component at a time (real parts, then imaginary
+// parts), so a window of W^2 values needs W^2 floats of LDS: two workgroups
+// per compute unit at W = 128 instead of one, so that one window's loads and
+// exchanges overlap another's arithmetic (8192 windows of W = 128, 16 bins:
+// 485 us, 2.2 TB/s of windows read, against 583 with whole complex values in
+// LDS; CBEDs of 5673 windows of W = 64: 49 against 55). Bound: the exchanges
+// and the bin sums, whose VALU work alone is 8 us per window and compute unit
+// where the loads take 6. Floats are padded by one in 32.
+__host__ __device__ constexpr int fl_padded(int n) { return n + (n >> 5); }
+__device__ __forceinline__ int flpad(int i) { return i + (i >> 5); }
+// Padded address of base + r STEP for the elements of one butterfly (r < R of
+// a sequence of length L): a compile-time offset from the padded base where
+// the elements' blocks of 32 do not depend on the base, i.e. STEP is a
+// multiple of 32, or base = m (R STEP) + k with k < STEP (Stockham stages of
+// rows) and R STEP divides 32 or is a multiple of it.
+template <int STEP, int R, int L>
+__device__ __forceinline__ int flpad_step(int base_padded, int base, int r) {
+  constexpr bool P2 = (STEP & (STEP - 1)) == 0 && (R & (R - 1)) == 0;
+  if constexpr (STEP % 32 == 0 || (P2 && 32 % (STEP * R) == 0) ||
+                (P2 && STEP * R % 32 == 0 && L % 32 == 0))
+    return base_padded + r * STEP + ((r * STEP) >> 5);
+  else
+    return flpad(base + r * STEP);
 }
 
-// 2D FFT of each W x W window in LDS, then either I(kw) = |Psi(kw)|^2 / W^2
-// summed over each bin's pixel list in FP64 (the lists encode the angle test
-// at full-grid frequency f kw), or (CBED) I written out in full. Workgroups
-// walk windows p = blockIdx.x, + gridDim.x, ... (one window each unless
-// there are more than PRISM_WD_GRID); window p belongs to the segment whose
-// range holds it (its own outputs and, for the sums, its own pixel lists).
-//
-// Bin sums: the lists are cut into chunks of kWdListChunk = 64 entries (one
-// per lane, kNoPix padding at the end of each bin); chunk k belongs to the
-// bin j with off[j] <= k < off[j + 1]. Wave w takes the contiguous chunks
-// [K w / NW, K (w + 1) / NW) of the K in all, so it meets only a few bins:
-// each lane sums its entry of the wave's chunks of a bin in order, one wave
-// sum per bin met goes to red[j][w] (zero for the bins a wave does not
-// meet), and the bin total adds red[j][0 .. NW) in order. The pixel indices
-// of kWdChunks chunks are loaded together, so the load latency is paid once
-// per group of chunks.
-template <int W, bool CBED>
-__global__ __launch_bounds__(wd_nt(W)) void k_window_detect(const float2* __restrict__ window,
-                                                            const float2* __restrict__ twW,
-                                                            const WindowSegs segs) {
-  constexpr int NT = wd_nt(W);
-  constexpr int NW = NT / 64;
-  // first row stage, applied from registers: radix 8 where W allows, else
-  // 4, 2 or 3 (W = 12, 36: 4; W = 18: 2)
-  constexpr int R0 = W % 8 == 0 ? 8 : (W % 4 == 0 ? 4 : (W % 2 == 0 ? 2 : 3));
+// Radix of the stage with span NS of a length-L transform (as fft_from).
+__host__ __device__ constexpr int next_radix(int rem) {
+  return rem % 8 == 0 ? 8 : (rem % 4 == 0 ? 4 : (rem % 2 == 0 ? 2 : 3));
+}
+
+// Flat index of element r of butterfly b's outputs / inputs in a stage.
+template <class B, int R, int NS>
+__host__ __device__ constexpr int out_index(int b, int r) {
+  constexpr int NB = B::L / R;
+  const int s = B::SEQ_FAST ? b % B::NSEQ : b / NB, j = B::SEQ_FAST ? b / B::NSEQ : b % NB;
+  const int k = j % NS, e = (j - k) * R + k + r * NS;
+  return (s / B::SPB) * B::BSTR + (s % B::SPB) * B::SSTR + e * B::ESTR;
+}
+template <class B, int R>
+__host__ __device__ constexpr int in_index(int b, int r) {
+  constexpr int NB = B::L / R;
+  const int s = B::SEQ_FAST ? b % B::NSEQ : b / NB, j = B::SEQ_FAST ? b / B::NSEQ : b % NB;
+  return (s / B::SPB) * B::BSTR + (s % B::SPB) * B::SSTR + (j + r * NB) * B::ESTR;
+}
+// Powers of two throughout: thread, butterfly and element numbers are
+// disjoint bit fields of the index, so padded addresses add up and all but
+// the thread's own part is a compile-time offset.
+template <class B, int NT>
+__host__ __device__ constexpr bool bit_fields() {
+  return (B::L & (B::L - 1)) == 0 && (B::NSEQ & (B::NSEQ - 1)) == 0 && (NT & (NT - 1)) == 0 &&
+         B::L * B::NSEQ >= 8 * NT;
+}
+
+// The window transforms' arithmetic with every multiply-add written out, so
+// that their results do not depend on what the compiler contracts in the code
+// around it: a b, and the 8- and 3-point DFTs of fft_lds.hpp (2 and 4 points
+// have no products). xb says which of the imaginary part's two products is
+// rounded on its own; it is chosen per butterfly (WinFft) so that
+// the detector sums, which are FP64, stay bit for bit what they were when the
+// choice was the compiler's.
+__device__ __forceinline__ float2 cmul_fma(float2 a, float2 b, bool xb) {
+  const float fx = xb ? a.x : a.y, fy = xb ? b.y : b.x;  // the fused pair
+  const float rx = xb ? a.y : a.x, ry = xb ? b.x : b.y;  // the rounded one
+  return make_float2(__builtin_fmaf(a.x, b.x, -(a.y * b.y)), __builtin_fmaf(fx, fy, rx * ry));
+}
+// z + s (x, y)
+__device__ __forceinline__ float2 madd(float2 z, float s, float x, float y) {
+  return make_float2(__builtin_fmaf(s, x, z.x), __builtin_fmaf(s, y, z.y));
+}
+template <int R>
+__device__ __forceinline__ void dft_fma(float2 (&v)[R]) {
+  if constexpr (R == 8) {
+    float2 e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6];
+    float2 o0 = v[1], o1 = v[3], o2 = v[5], o3 = v[7];
+    dft4v<false>(e0, e1, e2, e3);
+    dft4v<false>(o0, o1, o2, o3);
+    constexpr float r = 0.70710678118654752440f;
+    const float2 p = make_float2(o1.x + o1.y, o1.y - o1.x);      // o1 w / r
+    const float2 q = make_float2(o3.y - o3.x, -(o3.x + o3.y));   // o3 w^3 / r
+    o2 = mul_mi<false>(o2);
+    v[0] = cadd(e0, o0);
+    v[4] = csub(e0, o0);
+    v[1] = madd(e1, r, p.x, p.y);
+    v[5] = madd(e1, -r, p.x, p.y);
+    v[2] = cadd(e2, o2);
+    v[6] = csub(e2, o2);
+    v[3] = madd(e3, r, q.x, q.y);
+    v[7] = madd(e3, -r, q.x, q.y);
+  } else if constexpr (R == 3) {
+    constexpr float h = 0.86602540378443864676f;  // sqrt(3) / 2
+    const float2 t1 = cadd(v[1], v[2]), t2 = csub(v[1], v[2]);
+    const float2 m = madd(v[0], -0.5f, t1.x, t1.y);
+    v[0] = cadd(v[0], t1);
+    v[1] = madd(m, h, t2.y, -t2.x);
+    v[2] = madd(m, -h, t2.y, -t2.x);
+  } else {
+    dft<R, false>(v);
+  }
+}
+
+// Inputs of one butterfly times w^r, w = exp(-2 pi i k / (NS R)): w, w^2, w^4
+// from the table, the other powers as products (as stage_in).
+template <class B, int R, int NS>
+__device__ __forceinline__ void stage_twiddle(const float2* tw, int k, bool xb, float2 (&v)[R]) {
+  constexpr int TWS = B::L / (NS * R);
+  float2 w[R];
+  if constexpr (R == 2 || R == 4 || R == 8) {
+    w[1] = tw[k * TWS];
+    if constexpr (R >= 4) w[2] = tw[2 * k * TWS];
+    if constexpr (R == 4) w[3] = cmul_fma(w[1], w[2], false);
+    if constexpr (R == 8) {
+      w[4] = tw[4 * k * TWS];
+      w[3] = cmul_fma(w[1], w[2], false);
+      w[5] = cmul_fma(w[1], w[4], false);
+      w[6] = cmul_fma(w[2], w[4], false);
+      w[7] = cmul_fma(w[3], w[4], false);
+    }
+  } else {
+#pragma unroll
+    for (int r = 1; r < R; ++r) w[r] = tw[r * k * TWS];
+  }
+#pragma unroll
+  for (int r = 1; r < R; ++r)
+    v[r] = cmul_fma(v[r], w[r], xb && !(B::L == 128 && r == 4));
+}
+
+// Component Y of a stage's outputs to LDS / of its inputs from LDS (element
+// numbering of stage_out / stage_in).
+template <class B, int R, int NS, int NT, bool Y>
+__device__ __forceinline__ void put_part(float* lds, int tid,
+                                         const float2 (&v)[StageShape<B, R, NT>::PER][R]) {
+  using SS = StageShape<B, R, NT>;
+  if constexpr (bit_fields<B, NT>()) {
+    float* own = lds + flpad(out_index<B, R, NS>(tid, 0));
+#pragma unroll
+    for (int p = 0; p < SS::PER; ++p)
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        own[fl_padded(out_index<B, R, NS>(p * NT, r))] = Y ? v[p][r].y : v[p][r].x;
+  } else {
+#pragma unroll
+    for (int p = 0; p < SS::PER; ++p) {
+      const int b = tid + p * NT;
+      if (SS::GUARD && b >= SS::TOT) continue;
+      const int base = out_index<B, R, NS>(b, 0), pbase = flpad(base);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        lds[flpad_step<NS * B::ESTR, R, B::L>(pbase, base, r)] = Y ? v[p][r].y : v[p][r].x;
+    }
+  }
+}
+template <class B, int R, int NT, bool Y>
+__device__ __forceinline__ void get_part(const float* lds, int tid,
+                                         float2 (&v)[StageShape<B, R, NT>::PER][R]) {
+  using SS = StageShape<B, R, NT>;
+  auto set = [](float2& z, float x) {
+    if (Y) z.y = x;
+    else z.x = x;
+  };
+  if constexpr (bit_fields<B, NT>()) {
+    const float* own = lds + flpad(in_index<B, R>(tid, 0));
+#pragma unroll
+    for (int p = 0; p < SS::PER; ++p)
+#pragma unroll
+      for (int r = 0; r < R; ++r) set(v[p][r], own[fl_padded(in_index<B, R>(p * NT, r))]);
+  } else {
+#pragma unroll
+    for (int p = 0; p < SS::PER; ++p) {
+      const int b = tid + p * NT;
+      if (SS::GUARD && b >= SS::TOT) continue;
+      const int base = in_index<B, R>(b, 0), pbase = flpad(base);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        set(v[p][r], lds[flpad_step<SS::NB * B::ESTR, R, B::L>(pbase, base, r)]);
+    }
+  }
+}
+
+template <int W>
+struct WinFft {
+  static constexpr int NT = wd_nt(W);
   using Rows = RowBatch<W, W>;
   using Cols = Batch<W, W, W, 0, 1, W, true>;
-  using S8 = StageShape<Rows, R0, NT>;
-  __shared__ float2 lds[lds_padded(W * W)];
+
+  // xb of a stage's butterflies past the first NT: set where the stage's
+  // twiddles repeat every NT butterflies.
+  template <class B, int R, int NS>
+  __device__ __forceinline__ static constexpr bool round_xb() {
+    constexpr int NB = B::L / R;
+    return B::SEQ_FAST ? (W & (W - 1)) == 0 && (NT / W) % NS == 0
+                       : (NB & (NB - 1)) == 0 && NT % NB == 0;
+  }
+
+  // From the inputs v of the stage (B, NS) (twiddles applied) through the
+  // rest of the 2D transform; fin(v) gets the outputs of the last column
+  // stage (radix next_radix(W / span), see last_span).
+  template <class B, int NS, bool ROWS, class F>
+  __device__ __forceinline__ static void run(
+      float* lds, const float2* tw, int tid,
+      float2 (&v)[StageShape<B, next_radix(W / NS), NT>::PER][next_radix(W / NS)], const F& fin) {
+    constexpr int R = next_radix(W / NS);
+    using SS = StageShape<B, R, NT>;
+#pragma unroll
+    for (int p = 0; p < SS::PER; ++p)
+      if (!SS::GUARD || tid + p * NT < SS::TOT) dft_fma<R>(v[p]);
+    if constexpr (NS * R < W) {
+      pass<B, R, NS, B, NS * R, ROWS>(lds, tw, tid, v, fin);
+    } else if constexpr (ROWS) {
+      pass<B, R, NS, Cols, 1, false>(lds, tw, tid, v, fin);
+    } else {
+      fin(v);
+    }
+  }
+
+  template <class BO, int RO, int NSO, class BI, int NSI, bool ROWS, class F>
+  __device__ __forceinline__ static void pass(float* lds, const float2* tw, int tid,
+                                              float2 (&v)[StageShape<BO, RO, NT>::PER][RO],
+                                              const F& fin) {
+    constexpr int RI = next_radix(W / NSI);
+    using SI = StageShape<BI, RI, NT>;
+    float2 u[SI::PER][RI];
+    put_part<BO, RO, NSO, NT, false>(lds, tid, v);
+    __syncthreads();
+    get_part<BI, RI, NT, false>(lds, tid, u);
+    __syncthreads();
+    put_part<BO, RO, NSO, NT, true>(lds, tid, v);
+    __syncthreads();
+    get_part<BI, RI, NT, true>(lds, tid, u);
+    if constexpr (NSI > 1) {
+#pragma unroll
+      for (int p = 0; p < SI::PER; ++p) {
+        const int b = tid + p * NT;
+        if (SI::GUARD && b >= SI::TOT) continue;
+        int s, j;
+        stage_coords<BI, SI::NB>(b, s, j);
+        stage_twiddle<BI, RI, NSI>(tw, j % NSI, p > 0 && round_xb<BI, RI, NSI>(), u[p]);
+        // one butterfly's twiddles at a time: no registers for all of them
+        if constexpr (SI::PER * RI >= 24) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __syncthreads();  // LDS free for the next exchange
+    run<BI, NSI, ROWS>(lds, tw, tid, u, fin);
+  }
+};
+
+// Span of the last stage of a length-w transform (product of the radices
+// before it).
+__host__ __device__ constexpr int last_span(int w, int ns = 1) {
+  return ns * next_radix(w / ns) == w ? ns : last_span(w, ns * next_radix(w / ns));
+}
+
+// 2D FFT of each W x W window, then either I(kw) = |Psi(kw)|^2 / W^2 summed
+// over each bin's pixel list in FP64 (the lists encode the angle test at
+// full-grid frequency f kw), or (CBED) I written out in full. One workgroup
+// per window; window p belongs to the segment whose range holds it (its own
+// outputs and, for the sums, its own pixel lists).
+//
+// Bin sums: the squares of the real parts, then of the imaginary parts (each
+// in LDS in turn) are summed over the lists. The lists are cut into chunks of
+// kWdListChunk = 64 entries (one per lane, kNoPix padding at the end of each
+// bin); chunk k belongs to the bin j with off[j] <= k < off[j + 1]. Wave w
+// takes the contiguous chunks [K w / NW, K (w + 1) / NW) of the K in all, so
+// it meets only a few bins: each lane sums its entry of the wave's chunks of a
+// bin in order, one wave sum per bin met and component is added to red[j][w]
+// (zero for the bins a wave does not meet), and the bin total adds red[j][0 ..
+// NW) in order. The pixel indices of kWdChunks chunks are loaded together, so
+// the load latency is paid once per group of chunks.
+template <int W, bool CBED>
+__global__ __launch_bounds__(wd_nt(W)) __attribute__((amdgpu_waves_per_eu(wd_wpe(W))))
+void k_window_detect(const float2* __restrict__ window,
+                                                            const float2* __restrict__ twW,
+                                                            const WindowSegs segs) {
+  using WF = WinFft<W>;
+  using Rows = typename WF::Rows;
+  using Cols = typename WF::Cols;
+  constexpr int NT = WF::NT;
+  constexpr int NW = NT / 64;
+  constexpr int R0 = next_radix(W), NSL = last_span(W), RL = W / NSL;
+  using S0 = StageShape<Rows, R0, NT>;
+  using SL = StageShape<Cols, RL, NT>;
+  __shared__ float lds[fl_padded(W * W)];
   __shared__ float2 tw[W];
   __shared__ double red[CBED ? 1 : kMaxDet][NW];
   const int tid = threadIdx.x;
   load_twiddles<W, NT>(tw, twW, tid);
   const double inv_w2 = 1.0 / ((double)W * (double)W);
-#pragma unroll 1
-  for (int p = blockIdx.x; p < segs.total; p += gridDim.x) {
-    int k = 0;  // segment of window p (uniform)
-    while (k + 1 < segs.n && p >= segs.s[k + 1].begin) ++k;
-    const WindowSeg& sg = segs.s[k];
-    const int q = p - sg.begin;  // probe within the segment
-    float2 v[S8::PER][R0];
-    {
-      const float2* src = window + (size_t)p * W * W;
+  const int p = blockIdx.x;
+  int k = 0;  // segment of window p (uniform)
+  while (k + 1 < segs.n && p >= segs.s[k + 1].begin) ++k;
+  const WindowSeg& sg = segs.s[k];
+  const int q = p - sg.begin;  // probe within the segment
+  float2 v[S0::PER][R0];
+  {
+    const float2* src = window + (size_t)p * W * W;
 #pragma unroll
-      for (int c = 0; c < S8::PER; ++c) {
-        const int b = tid + c * NT;
-        if (!S8::GUARD || b < S8::TOT) {
-          int row, j;
-          stage_coords<Rows, S8::NB>(b, row, j);
+    for (int c = 0; c < S0::PER; ++c) {
+      const int b = tid + c * NT;
+      if (!S0::GUARD || b < S0::TOT) {
+        int row, j;
+        stage_coords<Rows, S0::NB>(b, row, j);
 #pragma unroll
-          for (int r = 0; r < R0; ++r) v[c][r] = src[row * W + j + r * (W / R0)];
-        }
+        for (int r = 0; r < R0; ++r) v[c][r] = src[row * W + j + r * (W / R0)];
       }
     }
-    stage_out<Rows, R0, 1, NT, false>(lds, tid, v);
-    __syncthreads();
-    fft_from<Rows, NT, false, R0>(lds, tw, tid);
-    fft_lds<Cols, NT, false>(lds, tw, tid);
+  }
+  WF::template run<Rows, 1, true>(lds, tw, tid, v, [&](float2(&z)[SL::PER][RL]) {
     if constexpr (CBED) {
       float* dst = sg.cbed + (size_t)q * W * W;
-      for (int e = tid; e < W * W; e += NT) {
-        const float2 z = lds[lpad(e)];
-        put_out(dst + e, ((double)z.x * z.x + (double)z.y * z.y) * inv_w2, sg.oa);
+#pragma unroll
+      for (int c = 0; c < SL::PER; ++c) {
+        const int b = tid + c * NT;
+        if (SL::GUARD && b >= SL::TOT) continue;
+        int s, j;
+        stage_coords<Cols, SL::NB>(b, s, j);
+#pragma unroll
+        for (int r = 0; r < RL; ++r)
+          put_out(dst + (j + r * NSL) * W + s,
+                  ((double)z[c][r].x * z[c][r].x + (double)z[c][r].y * z[c][r].y) * inv_w2,
+                  sg.oa);
       }
     } else {
       const uint16_t* __restrict__ pix = sg.pix;
@@ -297,39 +551,46 @@ __global__ __launch_bounds__(wd_nt(W)) void k_window_detect(const float2* __rest
       const int* off = lists->off;
       const int K = off[nb];  // chunks of kWdListChunk entries
       const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-      for (int i = tid; i < nb * NW; i += NT) red[i / NW][i % NW] = 0.0;
-      __syncthreads();
       const int c0 = (int)((long long)K * wv / NW), c1 = (int)((long long)K * (wv + 1) / NW);
-      int j = 0;  // bin of the current chunk (uniform in the wave)
-      while (j < nb && c0 >= off[j + 1]) ++j;
-      double acc = 0.0;
-      for (int k0 = c0; k0 < c1; k0 += kWdChunks) {
-        int px[kWdChunks];
+      for (int i = tid; i < nb * NW; i += NT) red[i / NW][i % NW] = 0.0;
+      auto sum_part = [&]() {
+        int j = 0;  // bin of the current chunk (uniform in the wave)
+        while (j < nb && c0 >= off[j + 1]) ++j;
+        double acc = 0.0;
+        for (int k0 = c0; k0 < c1; k0 += kWdChunks) {
+          int px[kWdChunks];
 #pragma unroll
-        for (int c = 0; c < kWdChunks; ++c)
-          px[c] = k0 + c < c1 ? (int)pix[(size_t)(k0 + c) * kWdListChunk + lane] : (int)kNoPix;
+          for (int c = 0; c < kWdChunks; ++c)
+            px[c] = k0 + c < c1 ? (int)pix[(size_t)(k0 + c) * kWdListChunk + lane] : (int)kNoPix;
 #pragma unroll
-        for (int c = 0; c < kWdChunks; ++c) {
-          const int kk = k0 + c;
-          if (kk < c1) {
-            if (kk >= off[j + 1]) {  // bin j ends: its wave sum, then the bin of chunk kk
-              const double sm = wave_sum(acc);
-              if (lane == 0) red[j][wv] = sm;
-              acc = 0.0;
-              do ++j;
-              while (kk >= off[j + 1]);
+          for (int c = 0; c < kWdChunks; ++c) {
+            const int kk = k0 + c;
+            if (kk < c1) {
+              if (kk >= off[j + 1]) {  // bin j ends: its wave sum, then the bin of chunk kk
+                const double sm = wave_sum(acc);
+                if (lane == 0) red[j][wv] += sm;
+                acc = 0.0;
+                do ++j;
+                while (kk >= off[j + 1]);
+              }
+              const bool ok = px[c] != (int)kNoPix;
+              const double x = (double)lds[flpad(ok ? px[c] : 0)];
+              acc += ok ? x * x : 0.0;
             }
-            const bool ok = px[c] != (int)kNoPix;
-            const float2 z = lds[lpad(ok ? px[c] : 0)];
-            const double I = (double)z.x * z.x + (double)z.y * z.y;
-            acc += ok ? I : 0.0;
           }
         }
-      }
-      if (c1 > c0) {
-        const double sm = wave_sum(acc);
-        if (lane == 0) red[j][wv] = sm;
-      }
+        if (c1 > c0) {
+          const double sm = wave_sum(acc);
+          if (lane == 0) red[j][wv] += sm;
+        }
+      };
+      put_part<Cols, RL, NSL, NT, false>(lds, tid, z);
+      __syncthreads();
+      sum_part();
+      __syncthreads();
+      put_part<Cols, RL, NSL, NT, true>(lds, tid, z);
+      __syncthreads();
+      sum_part();
       __syncthreads();
       if (tid < nb) {
         double sm = 0.0;
@@ -337,8 +598,7 @@ __global__ __launch_bounds__(wd_nt(W)) void k_window_detect(const float2* __rest
         put_out(sg.out + (size_t)q * nb + tid, sm * inv_w2, sg.oa);
       }
     }
-    __syncthreads();  // LDS free for the next window
-  }
+  });
 }
 
 inline unsigned blocks_for(size_t n, unsigned bs) { return (unsigned)((n + bs - 1) / bs); }
@@ -422,17 +682,13 @@ hipError_t launch_window_big(float2* window, int np, int w, const float2* twW, i
   return hipGetLastError();
 }
 
-// Workgroups for the window kernels: one per probe up to PRISM_WD_GRID, then
-// each walks several probes.
-static unsigned window_grid(int np) { return (unsigned)std::min(np, PRISM_WD_GRID); }
-
 hipError_t launch_window_detect(const float2* window, const WindowSegs& segs, int w,
                                 const float2* twW, hipStream_t st) {
   if (segs.total <= 0) return hipSuccess;
   if (segs.n < 1 || segs.n > kMaxSeg) return hipErrorInvalidValue;
 #define WD(WW)                                                                          \
   case WW:                                                                              \
-    hipLaunchKernelGGL((k_window_detect<WW, false>), dim3(window_grid(segs.total)),     \
+    hipLaunchKernelGGL((k_window_detect<WW, false>), dim3((unsigned)segs.total),     \
                        dim3(wd_nt(WW)), 0, st, window, twW, segs);                      \
     break;
   switch (w) {
@@ -461,7 +717,7 @@ hipError_t launch_window_cbed(const float2* window, const WindowSegs& segs, int 
   if (segs.n < 1 || segs.n > kMaxSeg) return hipErrorInvalidValue;
 #define WC(WW)                                                                          \
   case WW:                                                                              \
-    hipLaunchKernelGGL((k_window_detect<WW, true>), dim3(window_grid(segs.total)),      \
+    hipLaunchKernelGGL((k_window_detect<WW, true>), dim3((unsigned)segs.total),      \
                        dim3(wd_nt(WW)), 0, st, window, twW, segs);                      \
     break;
   switch (w) {

@@ -103,3 +103,25 @@ def test_fp32_against_oracle(n, f, alpha):
     ref = O.prism_outputs(S.cpu().numpy().astype(np.complex128), plan.beams(f, amax), f, 0.1 * n,
                           80.0, dict(alpha_mrad=alpha, C1_A=25.0, C3_A=0.0), xy, EDGES)
     assert np.linalg.norm(D - ref) <= 5e-6 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("n,f", [(128, 8), (192, 8), (128, 4), (576, 16), (192, 4), (128, 2),
+                                 (576, 8), (384, 4), (256, 2), (576, 4), (384, 2), (512, 2)])
+def test_every_window_side(n, f):
+    """Detector sums and CBEDs of W = 8 .. 128 against the oracle's on the same S-matrix
+    (tolerance as above), and against each other (FP64 sums of FP32 patterns)."""
+    alpha = 14.0
+    plan, amax, S = _case(n, f, alpha)
+    w = n // (2 * f)
+    rng = np.random.default_rng([n, f, 13])
+    xy = np.concatenate([_near(n, 3, rng), rng.uniform(0.0, 0.1 * n, (2, 2))])
+    D = _run(plan, f, amax, S, xy, alpha)
+    C = _run(plan, f, amax, S, xy, alpha, cbed=True).astype(np.float64)
+    o = dict(alpha_mrad=alpha, C1_A=25.0, C3_A=0.0)
+    ref = O.prism_outputs(S.cpu().numpy().astype(np.complex128), plan.beams(f, amax), f, 0.1 * n,
+                          80.0, o, xy, EDGES)
+    assert np.linalg.norm(D - ref) <= 5e-6 * np.linalg.norm(ref)
+    k = np.fft.fftfreq(w, 1.0 / w) * f
+    th = O.wavelength(80.0) / (0.1 * n) * np.sqrt(k[:, None] ** 2 + k[None, :] ** 2) * 1e3
+    sums = np.stack([(C * ((th >= lo) & (th < hi))).sum(axis=(1, 2)) for lo, hi in EDGES], axis=1)
+    assert np.linalg.norm(D - sums) <= 1e-6 * np.linalg.norm(sums)
