@@ -166,8 +166,9 @@ int prism_probe_order(const prism_plan* plan, int f, const double* probe_xy_host
  * packs the active beams of the S-matrix into a pixel-major 16-bit copy in
  * the workspace (FP16: each beam scaled by an exact power of two so that its
  * largest component is below 1, the coefficient divided by the same factor;
- * BF16 has FP32's range and takes the values as they are) and runs the window sum on 16-bit matrix cores with FP32 accumulation;
- * everything after the window sum stays FP32/FP64. The workspace sizes
+ * BF16 has FP32's range and takes the values as they are) and runs the
+ * window sum on 16-bit matrix cores with FP32 accumulation; everything after
+ * the window sum stays FP32/FP64. The workspace sizes
  * returned by prism_probe_workspace_bytes follow the plan's precision, so
  * query them after this call. Setting the precision is not stream-ordered:
  * do it between calls. */
@@ -493,8 +494,9 @@ int prism_server_call_stats(const prism_server* server, long long* probe_calls,
  *     has where there is that much work (512, 256);
  *   wave_chunk_mib: wave state per slice-pass launch, which sets the
  *     preferred build and multislice workspaces (16 .. 65536; 256);
- *   probe_group: probes per window-sum group (16, 32, 64; 0: 64 for
- *     W >= 128, 32 for W >= 64, else 16), which also sets the tile shape
+ *   probe_group: probes per window-sum group (16, 32, 64; 0: with FP32
+ *     operands 64 for W >= 128, 32 for W >= 64, else 16; with 16-bit operands
+ *     64 for W >= 48, else 16), which also sets the tile shape
  *     prism_probe_group reports;
  *   window_tile_div: window-sum workgroups per probe group are the 128-pixel
  *     tiles of one window divided by this (1 .. 64; 4), or more where a launch
@@ -511,7 +513,8 @@ typedef struct {
   int window_tile_div;
 } prism_tuning;
 int prism_set_tuning(prism_plan* plan, const prism_tuning* tuning);
-/* The plan's effective launch shapes (probe_group 0: chosen by W). */
+/* The plan's effective launch shapes (probe_group 0: chosen by W and the
+ * operand type). */
 int prism_get_tuning(const prism_plan* plan, prism_tuning* tuning);
 
 /* Per-kernel timing: while enabled, every kernel launch of this plan is

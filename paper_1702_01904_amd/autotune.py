@@ -6,9 +6,10 @@ slices, 0.1 A pixels, 80 keV, 20 mrad, 8 slices of 2 A; the (n/4)^2 probe
 raster at two S-matrix pixels in probe-tile order) under candidate launch
 shapes, one parameter at a time (each starting from the best found so far):
 
-  build: row_iters, row_min_groups, col_iters, col_min_groups (the four-step
-         slice passes, n = 256 and 1024), wave_chunk_mib (every n);
-  probe: probe_group, window_tile_div.
+  build: row_iters, row_min_groups, col_iters, col_min_groups, wave_chunk_mib;
+  probe: window_tile_div (probe_group stays 0: the best group depends on the
+         window side and the operand type, which the library's rule knows and a
+         table by grid does not).
 
 A candidate is kept only if its S-matrix and probe outputs equal the default
 shapes' bit for bit (none of these shapes may change a result). The winners
@@ -32,9 +33,8 @@ FIELDS = ("row_iters", "row_min_groups", "col_iters", "col_min_groups", "wave_ch
           "probe_group", "window_tile_div")
 BUILD_SWEEP = [("row_iters", (2, 4, 8, 16, 32)), ("row_min_groups", (128, 256, 512, 1024)),
                ("col_iters", (2, 4, 8, 16)), ("col_min_groups", (128, 256, 512, 1024)),
-               ("wave_chunk_mib", (64, 128, 256, 512))]
-PROBE_SWEEP = [("probe_group", (16, 32, 64)), ("window_tile_div", (1, 2, 4, 8))]
-FOUR_STEP = (256, 1024)
+               ("wave_chunk_mib", (64, 128, 192, 256, 512))]
+PROBE_SWEEP = [("window_tile_div", (1, 2, 4, 8))]
 
 
 def interp_factor(n):
@@ -100,8 +100,7 @@ def tune_grid(n, log):
     defaults = plan.tuning()
     ref_ms, ref_S = run(best, "build")
     base_build = ref_ms
-    sweeps = [s for s in BUILD_SWEEP if n in FOUR_STEP or s[0] == "wave_chunk_mib"]
-    for name, values in sweeps:
+    for name, values in BUILD_SWEEP:
         for v in values:
             cand = dict(best, **{name: v})
             ms, Sc = run(cand, "build")

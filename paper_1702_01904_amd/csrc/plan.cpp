@@ -349,10 +349,6 @@ int pref_wave_chunk(const prism_plan* p, int count) {
   return std::max(1, std::min(c, count));
 }
 
-// probes per window-sum group for window side w
-int group_of(const prism_plan* p, int w) {
-  return p->probe_group > 0 ? p->probe_group : prism::contract_group(w);
-}
 
 struct SliceWs {
   float2* twN;
@@ -394,6 +390,11 @@ int choose_chunk(const prism_plan* p, int want, int n_beams, int n_det, size_t w
 prism::Prec packed_prec(int prec) {
   return prec == PRISM_PREC_BF16 ? prism::Prec::kBF16
                                  : (prec == PRISM_PREC_FP16 ? prism::Prec::kFP16 : prism::Prec::kF32);
+}
+
+// probes per window-sum group for window side w
+int group_of(const prism_plan* p, int w) {
+  return p->probe_group > 0 ? p->probe_group : prism::contract_group(w, packed_prec(p->prec));
 }
 
 // Active beams padded to whole K blocks.

@@ -605,7 +605,19 @@ inline unsigned blocks_for(size_t n, unsigned bs) { return (unsigned)((n + bs - 
 
 }  // namespace
 
-int contract_group(int w) { return w >= 128 ? kCG128 : (w >= 64 ? 32 : 16); }
+// A group shares one union window, so a larger one reads fewer S-matrix pixels
+// per probe and pays for the union's pixels that a member does not have. FP32
+// is bound by its products, which a union wastes: 64 only where windows are
+// large against the scan step. 16-bit operands are bound by what they read:
+// 64 as soon as a window is three tiles wide. Measured (window sum, groups of
+// 16 / 32 / 64, 12800 raster probes): FP32 W = 64 722 / 660 / 770 us, W = 96
+// 2767 / 2628 / 2943 us, W = 144 13.8 / 13.1 / 11.8 ms; BF16 W = 48 94 / 85 /
+// 78 us, W = 64 205 / 176 / 156 us, W = 128 2569 / 1666 / 1236 us; 1280 probes
+// at W = 24: FP32 16 / 17 / 22, BF16 11 / 11 / 15 us.
+int contract_group(int w, Prec pr) {
+  if (pr != Prec::kF32) return w >= 48 ? 64 : 16;
+  return w >= 128 ? kCG128 : (w >= 64 ? 32 : 16);
+}
 
 int contract_tile_slots(int w, int window_tile_div, int groups) {
   const int own = (w * w + kCTile - 1) / kCTile;  // tiles of one window

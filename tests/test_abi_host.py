@@ -490,6 +490,19 @@ def test_noalloc_rejects_probe_steps_beyond_its_scratch():
     assert r == _native.PRISM_EINVAL
 
 
+@pytest.mark.parametrize("f,w,fp32,b16", [(4, 128, 64, 64), (6, 64, 32, 64), (8, 48, 16, 64),
+                                          (16, 36, 16, 16), (4, 144, 64, 64), (16, 24, 16, 16)])
+def test_default_probe_group_follows_the_operands(f, w, fp32, b16):
+    n = 2 * f * w
+    p = _plan(n, 0.1 * n, 80.0, 2)
+    for prec, want in (("fp32", fp32), ("bf16", b16), ("fp16", b16)):
+        p.set_probe_precision(prec)
+        assert p.probe_group(f)[0] == want
+        p.set_tuning(dict(probe_group=32))
+        assert p.probe_group(f)[0] == 32
+        p.set_tuning({})
+
+
 def test_tuning_roundtrip_and_validation():
     p = _plan(1024, 40.0, 200.0, 2)
     p.set_tuning({})
