@@ -496,7 +496,8 @@ int prism_server_call_stats(const prism_server* server, long long* probe_calls,
  *     preferred build and multislice workspaces (16 .. 65536; 256);
  *   probe_group: probes per window-sum group (16, 32, 64; 0: with FP32
  *     operands 64 for W >= 128, 32 for W >= 64, else 16; with 16-bit operands
- *     64 for W >= 48, else 16), which also sets the tile shape
+ *     64 for W >= 48, else 16, and smaller groups down to 16 on a workspace
+ *     that does not hold that many windows), which also sets the tile shape
  *     prism_probe_group reports;
  *   window_tile_div: window-sum workgroups per probe group are the 128-pixel
  *     tiles of one window divided by this (1 .. 64; 4), or more where a launch

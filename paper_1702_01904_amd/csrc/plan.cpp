@@ -397,6 +397,12 @@ int group_of(const prism_plan* p, int w) {
   return p->probe_group > 0 ? p->probe_group : prism::contract_group(w, packed_prec(p->prec));
 }
 
+// the group on a workspace that holds no group_of() probes: the chosen one
+// shrinks (the same results, fewer probes per union window), a set one stays
+int least_group(const prism_plan* p, int w) {
+  return p->probe_group > 0 ? p->probe_group : std::min(16, group_of(p, w));
+}
+
 // Active beams padded to whole K blocks.
 int padded_beams(int n_act, prism::Prec pk) {
   const int pad = prism::prec_block_beams(pk);
@@ -820,11 +826,16 @@ int run_class(std::vector<Req>& rq, const std::vector<int>& members, void* ws, s
     }
     if (sb.reqs.empty()) {
       // the next request alone, on fewer probes per chunk
+      Req& r = rq[members[i]];
       sb.add(rq, members[i]);
       chunk = chunk_for(sb.probes);
       while (chunk >= G && sb.layout(rq, chunk, &probe_ws, nullptr) > ws_bytes)
         chunk = chunk > 8 * G ? (chunk * 3 / 4) / G * G : chunk - G;
-      if (chunk < G) return fail(PRISM_ENOSPACE, "workspace smaller than the probe-step minimum");
+      while (chunk < r.G && r.G > least_group(r.p, r.w)) {
+        r.G /= 2;
+        chunk = sb.layout(rq, r.G, &probe_ws, nullptr) > ws_bytes ? 0 : r.G;
+      }
+      if (chunk < r.G) return fail(PRISM_ENOSPACE, "workspace smaller than the probe-step minimum");
     }
     if (int e = run_sub(rq, sb, chunk, base, st)) return e;
     i += sb.reqs.size();
@@ -1104,7 +1115,8 @@ int prism_probe_workspace_bytes(const prism_plan* cp, int f, double amax_mrad,
   const int n_lists = prism::window_big(w) ? 0 : 1;
   ProbeBatchWs bw;
   *pref = probe_batch_layout(w, G, pk, shapes, n_lists, 1, pref_probe_chunk(w, G), &bw, nullptr);
-  *minimum = probe_batch_layout(w, G, pk, shapes, n_lists, 1, G, &bw, nullptr);
+  const int g0 = least_group(p, w);
+  *minimum = probe_batch_layout(w, g0, pk, shapes, n_lists, 1, g0, &bw, nullptr);
   return PRISM_OK;
 }
 
@@ -1357,7 +1369,10 @@ int prism_probe_batch_workspace_bytes(const prism_probe_request* requests, int c
   for (size_t i = 0; i < rq.size(); ++i) {
     Sub one;
     one.add(rq, (int)i);
-    *minimum = std::max(*minimum, one.layout(rq, rq[i].G, &bw, nullptr));
+    const int G0 = rq[i].G, g0 = least_group(rq[i].p, rq[i].w);
+    rq[i].G = g0;
+    *minimum = std::max(*minimum, one.layout(rq, g0, &bw, nullptr));
+    rq[i].G = G0;
     if (done[i]) continue;
     Sub cls;  // every request of i's launch class
     for (size_t j = i; j < rq.size(); ++j)

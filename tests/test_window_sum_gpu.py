@@ -28,13 +28,13 @@ def _case(n, f, alpha, seed=3):
     return plan, amax, S
 
 
-def _run(plan, f, amax, S, xy, alpha, cbed=False):
+def _run(plan, f, amax, S, xy, alpha, cbed=False, ws_bytes=None):
     import torch
     o = dict(alpha_mrad=alpha, C1_A=25.0)
     pos = G.upload(xy)
     w = plan.n // (2 * f)
-    ws = torch.full((plan.probe_workspace_bytes(f, amax, o)[0],), 255, dtype=torch.uint8,
-                    device=G.device())
+    size = ws_bytes or plan.probe_workspace_bytes(f, amax, o)[0]
+    ws = torch.full((size,), 255, dtype=torch.uint8, device=G.device())
     G.say(f"window sum n={plan.n} f={f} P={len(xy)} B={S.shape[0]} cbed={cbed}")
     if cbed:
         out = torch.full((len(xy), w, w), float("nan"), dtype=torch.float32, device=G.device())
@@ -71,6 +71,28 @@ def test_groupings_agree(n, f, alpha, prec):
                 if base is None:
                     base = _run(plan, f, amax, S, xy, alpha)
                 assert np.array_equal(D, base[:count]), (group, div, count)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp16"])
+@pytest.mark.parametrize("n,f", [(256, 1), (256, 2), (384, 4), (128, 4)])
+def test_small_workspaces_shrink_the_group(n, f, prec):
+    """W = 128, 64, 48, 16 from the smallest workspace up to one that holds a full group:
+    the same bits; one 16-probe window less is refused."""
+    from paper_1702_01904_amd import PrismError
+    alpha = 10.0
+    plan, amax, S = _case(n, f, alpha)
+    plan.set_tuning({})
+    plan.set_probe_precision(prec)
+    rng = np.random.default_rng([n, f, 17])
+    xy = np.concatenate([_near(n, 40, rng), rng.uniform(0.0, 0.1 * n, (31, 2))])
+    full = _run(plan, f, amax, S, xy, alpha)
+    least = plan.probe_workspace_bytes(f, amax, dict(alpha_mrad=alpha, C1_A=25.0))[1]
+    window = 8 * (n // (2 * f)) ** 2
+    for more in (0, 15 * window, 40 * window, 100 * window):
+        D = _run(plan, f, amax, S, xy, alpha, ws_bytes=least + more)
+        assert np.array_equal(D, full), more
+    with pytest.raises(PrismError):
+        _run(plan, f, amax, S, xy, alpha, ws_bytes=least - window)
 
 
 @pytest.mark.parametrize("prec", ["fp32", "bf16"])
