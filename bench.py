@@ -40,10 +40,10 @@ CONFIG = "fcc1024"
 # write x1.0), as in the HBM-traffic summary under profiles/. Valid only for
 # the kernel sources with this hash (of their code, comments aside); reported
 # as null otherwise.
-TRAFFIC_SRC_SHA = "a81852979c72bdc3"
-TRAFFIC_BYTES = {"row_pass": 563499446, "col_pass": 521796428, "contract": 9375558529,
-                 "s32_pack": 1310732154, "window_detect": 1079331347, "contract16": 4706686928,
-                 "s16_pack": 975213709}
+TRAFFIC_SRC_SHA = "175adbe2521e172b"
+TRAFFIC_BYTES = {"row_pass": 426327492, "col_pass": 391434107, "contract": 4440993601,
+                 "s32_pack": 1310761703, "window_detect": 1141250572, "contract16": 2355982813,
+                 "s16_pack": 975254243}
 
 
 # Sources that decide the profiled kernels and their launch shapes (the

@@ -246,8 +246,8 @@ int prism_probe_outputs(prism_plan* plan, int f, double alpha_max_mrad, const vo
  * the process ends). Results equal prism_probe_outputs'.
  * Limit: PRISM_ENOSPACE, before anything is enqueued, when the probe step's
  * minimum workspace (prism_probe_workspace_bytes) exceeds the array, e.g.
- * 305 active beams on a 512^2 S-matrix (649 MiB in FP32, 329 MiB in BF16);
- * 69 active beams at 512^2 need 163 MiB. Other errors as
+ * 305 active beams on a 512^2 S-matrix (643 MiB in FP32, 323 MiB in BF16);
+ * 69 active beams at 512^2 need 161 MiB. Other errors as
  * prism_probe_outputs.
  * Every call on one GPU shares that GPU's array, and it keeps the last
  * call's contents: calls that overlap on one GPU (other streams, other host
