@@ -1259,25 +1259,33 @@ int prism_build_smatrix(prism_plan* p, int f, double amax_mrad, void* S, size_t 
     HIP_TRY(hipEventRecord(p->fork_ev, st), "fork build stream");
     HIP_TRY(hipStreamWaitEvent(p->aux, p->fork_ev, 0), "fork build stream");
   }
-  int g = 0;
-  for (int b0 = 0; b0 < B; b0 += sub, ++g) {
-    const int nb = std::min(sub, B - b0);
-    hipStream_t sg = ls[g % lanes];
-    float2* state = w.state + (size_t)(g % lanes) * sub * n * (n / 2);
-    const prism::BeamWaves init{w.mn, b0, f};  // the first row pass forms the plane waves
-    for (int s = 0; s < p->H; ++s) {
-      LAUNCH(p, sg, "row_pass",
-             prism::launch_row_pass(state, nb, n, w.trans + (size_t)s * n * n, w.twN, w.tw2,
-                                    p->tune, sg, s == 0 ? &init : nullptr));
-      LAUNCH(p, sg, "col_pass", prism::launch_col_pass(state, nb, n, w.prop + (size_t)s * n, w.twN, w.tw2, p->tune, sg));
+  auto run_lanes = [&]() -> int {
+    int g = 0;
+    for (int b0 = 0; b0 < B; b0 += sub, ++g) {
+      const int nb = std::min(sub, B - b0);
+      hipStream_t sg = ls[g % lanes];
+      float2* state = w.state + (size_t)(g % lanes) * sub * n * (n / 2);
+      const prism::BeamWaves init{w.mn, b0, f};  // the first row pass forms the plane waves
+      for (int s = 0; s < p->H; ++s) {
+        LAUNCH(p, sg, "row_pass",
+               prism::launch_row_pass(state, nb, n, w.trans + (size_t)s * n * n, w.twN, w.tw2,
+                                      p->tune, sg, s == 0 ? &init : nullptr));
+        LAUNCH(p, sg, "col_pass", prism::launch_col_pass(state, nb, n, w.prop + (size_t)s * n, w.twN, w.tw2, p->tune, sg));
+      }
+      LAUNCH(p, sg, "extract", prism::launch_extract(state, nb, n, Sout + (size_t)b0 * splane, w.twH, sg));
     }
-    LAUNCH(p, sg, "extract", prism::launch_extract(state, nb, n, Sout + (size_t)b0 * splane, w.twH, sg));
-  }
+    return PRISM_OK;
+  };
+  const int status = run_lanes();
+  // joined after an error too: the passes already queued on the second stream
+  // still use the workspace and S, which the caller may free or reuse in the
+  // order of its own stream
   if (lanes == 2) {
-    HIP_TRY(hipEventRecord(p->join_ev, p->aux), "join build stream");
-    HIP_TRY(hipStreamWaitEvent(st, p->join_ev, 0), "join build stream");
+    hipError_t e = hipEventRecord(p->join_ev, p->aux);
+    if (e == hipSuccess) e = hipStreamWaitEvent(st, p->join_ev, 0);
+    if (e != hipSuccess && status == PRISM_OK) return hip_fail(e, "join build stream");
   }
-  return PRISM_OK;
+  return status;
 }
 
 int prism_multislice_outputs(prism_plan* p, const double* xy, int P, const prism_optics* o,
