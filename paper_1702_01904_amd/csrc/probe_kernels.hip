@@ -223,30 +223,55 @@ __host__ __device__ constexpr int wd_nt(int w) {
 // 16 waves (64 registers).
 __host__ __device__ constexpr int wd_wpe(int w) { return w == 128 ? 8 : 6; }
 
-// The window transforms keep the window in registers and pass it from stage
-// to stage through LDS one component at a time (real parts, then imaginary
-// parts), so a window of W^2 values needs W^2 floats of LDS: two workgroups
-// per compute unit at W = 128 instead of one, so that one window's loads and
-// exchanges overlap another's arithmetic (8192 windows of W = 128, 16 bins:
-// 485 us, 2.2 TB/s of windows read, against 583 with whole complex values in
-// LDS; CBEDs of 5673 windows of W = 64: 49 against 55). Bound: the exchanges
-// and the bin sums, whose VALU work alone is 8 us per window and compute unit
-// where the loads take 6. Floats are padded by one in 32.
-__host__ __device__ constexpr int fl_padded(int n) { return n + (n >> 5); }
-__device__ __forceinline__ int flpad(int i) { return i + (i >> 5); }
+// The window transforms keep the window in registers and pass it from stage to
+// stage through LDS, as whole complex values or one component at a time (real
+// parts, then imaginary parts). By components a window needs half of the LDS, at
+// four barriers per exchange instead of two and two walks of the bin lists. That
+// pays where LDS or its traffic limits the waves in flight: at W = 128, where
+// whole values let one workgroup per compute unit run instead of two (8192
+// windows, 16 bins: 583 -> 485 us), and, with registers for two workgroups of
+// nine waves either way, still at W = 96 (12800 windows, 3 bins: 589 us against
+// 608 whole; patterns 412 against 482). Below, whole values are faster: W = 8, 16
+// bins 26.6 us against 46.9; W = 32, 16 bins 56.6 against 92.5; W = 36, 3 bins
+// 55 against 82; W = 64, 3 bins 116 against 137; W = 72, 3 bins 269 against 330,
+// though patterns of W = 72 take 220 against 208 (12800 windows each).
+__host__ __device__ constexpr bool wd_whole(int w, bool cbed) { return w <= (cbed ? 64 : 72); }
+enum class Part { kRe, kIm, kWhole };
+template <Part PT>
+struct LdsPart {
+  using T = float;
+  static constexpr int SH = 5;  // padding: one element in 2^SH
+  __device__ __forceinline__ static T of(float2 z) { return PT == Part::kRe ? z.x : z.y; }
+  __device__ __forceinline__ static void to(float2& z, T x) {
+    if (PT == Part::kRe) z.x = x;
+    else z.y = x;
+  }
+};
+template <>
+struct LdsPart<Part::kWhole> {
+  using T = float2;
+  static constexpr int SH = 4;
+  __device__ __forceinline__ static T of(float2 z) { return z; }
+  __device__ __forceinline__ static void to(float2& z, T x) { z = x; }
+};
+template <int SH>
+__host__ __device__ constexpr int padded(int i) {
+  return i + (i >> SH);
+}
 // Padded address of base + r STEP for the elements of one butterfly (r < R of
 // a sequence of length L): a compile-time offset from the padded base where
-// the elements' blocks of 32 do not depend on the base, i.e. STEP is a
-// multiple of 32, or base = m (R STEP) + k with k < STEP (Stockham stages of
-// rows) and R STEP divides 32 or is a multiple of it.
-template <int STEP, int R, int L>
-__device__ __forceinline__ int flpad_step(int base_padded, int base, int r) {
+// the elements' blocks of P = 2^SH do not depend on the base, i.e. STEP is a
+// multiple of P, or base = m (R STEP) + k with k < STEP (Stockham stages of
+// rows) and R STEP divides P or is a multiple of it.
+template <int SH, int STEP, int R, int L>
+__device__ __forceinline__ int padded_step(int base_padded, int base, int r) {
+  constexpr int P = 1 << SH;
   constexpr bool P2 = (STEP & (STEP - 1)) == 0 && (R & (R - 1)) == 0;
-  if constexpr (STEP % 32 == 0 || (P2 && 32 % (STEP * R) == 0) ||
-                (P2 && STEP * R % 32 == 0 && L % 32 == 0))
-    return base_padded + r * STEP + ((r * STEP) >> 5);
+  if constexpr (STEP % P == 0 || (P2 && P % (STEP * R) == 0) ||
+                (P2 && STEP * R % P == 0 && L % P == 0))
+    return base_padded + r * STEP + ((r * STEP) >> SH);
   else
-    return flpad(base + r * STEP);
+    return padded<SH>(base + r * STEP);
 }
 
 // Radix of the stage with span NS of a length-L transform (as fft_from).
@@ -344,61 +369,63 @@ __device__ __forceinline__ void stage_twiddle(const float2* tw, int k, float2 (&
   for (int r = 1; r < R; ++r) v[r] = cmul_fma(v[r], w[r]);
 }
 
-// Component Y of a stage's outputs to LDS / of its inputs from LDS (element
+// Part PT of a stage's outputs to LDS / of its inputs from LDS (element
 // numbering of stage_out / stage_in).
-template <class B, int R, int NS, int NT, bool Y>
-__device__ __forceinline__ void put_part(float* lds, int tid,
+template <class B, int R, int NS, int NT, Part PT>
+__device__ __forceinline__ void put_part(typename LdsPart<PT>::T* lds, int tid,
                                          const float2 (&v)[StageShape<B, R, NT>::PER][R]) {
   using SS = StageShape<B, R, NT>;
+  using LP = LdsPart<PT>;
   if constexpr (bit_fields<B, NT>()) {
-    float* own = lds + flpad(out_index<B, R, NS>(tid, 0));
+    typename LP::T* own = lds + padded<LP::SH>(out_index<B, R, NS>(tid, 0));
 #pragma unroll
     for (int p = 0; p < SS::PER; ++p)
 #pragma unroll
       for (int r = 0; r < R; ++r)
-        own[fl_padded(out_index<B, R, NS>(p * NT, r))] = Y ? v[p][r].y : v[p][r].x;
+        own[padded<LP::SH>(out_index<B, R, NS>(p * NT, r))] = LP::of(v[p][r]);
   } else {
 #pragma unroll
     for (int p = 0; p < SS::PER; ++p) {
       const int b = tid + p * NT;
       if (SS::GUARD && b >= SS::TOT) continue;
-      const int base = out_index<B, R, NS>(b, 0), pbase = flpad(base);
+      const int base = out_index<B, R, NS>(b, 0), pbase = padded<LP::SH>(base);
 #pragma unroll
       for (int r = 0; r < R; ++r)
-        lds[flpad_step<NS * B::ESTR, R, B::L>(pbase, base, r)] = Y ? v[p][r].y : v[p][r].x;
+        lds[padded_step<LP::SH, NS * B::ESTR, R, B::L>(pbase, base, r)] = LP::of(v[p][r]);
     }
   }
 }
-template <class B, int R, int NT, bool Y>
-__device__ __forceinline__ void get_part(const float* lds, int tid,
+template <class B, int R, int NT, Part PT>
+__device__ __forceinline__ void get_part(const typename LdsPart<PT>::T* lds, int tid,
                                          float2 (&v)[StageShape<B, R, NT>::PER][R]) {
   using SS = StageShape<B, R, NT>;
-  auto set = [](float2& z, float x) {
-    if (Y) z.y = x;
-    else z.x = x;
-  };
+  using LP = LdsPart<PT>;
   if constexpr (bit_fields<B, NT>()) {
-    const float* own = lds + flpad(in_index<B, R>(tid, 0));
+    const typename LP::T* own = lds + padded<LP::SH>(in_index<B, R>(tid, 0));
 #pragma unroll
     for (int p = 0; p < SS::PER; ++p)
 #pragma unroll
-      for (int r = 0; r < R; ++r) set(v[p][r], own[fl_padded(in_index<B, R>(p * NT, r))]);
+      for (int r = 0; r < R; ++r)
+        LP::to(v[p][r], own[padded<LP::SH>(in_index<B, R>(p * NT, r))]);
   } else {
 #pragma unroll
     for (int p = 0; p < SS::PER; ++p) {
       const int b = tid + p * NT;
       if (SS::GUARD && b >= SS::TOT) continue;
-      const int base = in_index<B, R>(b, 0), pbase = flpad(base);
+      const int base = in_index<B, R>(b, 0), pbase = padded<LP::SH>(base);
 #pragma unroll
       for (int r = 0; r < R; ++r)
-        set(v[p][r], lds[flpad_step<SS::NB * B::ESTR, R, B::L>(pbase, base, r)]);
+        LP::to(v[p][r], lds[padded_step<LP::SH, SS::NB * B::ESTR, R, B::L>(pbase, base, r)]);
     }
   }
 }
 
-template <int W>
+template <int W, bool WHOLE>
 struct WinFft {
   static constexpr int NT = wd_nt(W);
+  using Lds = LdsPart<WHOLE ? Part::kWhole : Part::kRe>;
+  using T = typename Lds::T;
+  static constexpr int SIZE = padded<Lds::SH>(W * W);
   using Rows = RowBatch<W, W>;
   using Cols = Batch<W, W, W, 0, 1, W, true>;
 
@@ -407,7 +434,7 @@ struct WinFft {
   // stage (radix next_radix(W / span), see last_span).
   template <class B, int NS, bool ROWS, class F>
   __device__ __forceinline__ static void run(
-      float* lds, const float2* tw, int tid,
+      T* lds, const float2* tw, int tid,
       float2 (&v)[StageShape<B, next_radix(W / NS), NT>::PER][next_radix(W / NS)], const F& fin) {
     constexpr int R = next_radix(W / NS);
     using SS = StageShape<B, R, NT>;
@@ -424,19 +451,25 @@ struct WinFft {
   }
 
   template <class BO, int RO, int NSO, class BI, int NSI, bool ROWS, class F>
-  __device__ __forceinline__ static void pass(float* lds, const float2* tw, int tid,
+  __device__ __forceinline__ static void pass(T* lds, const float2* tw, int tid,
                                               float2 (&v)[StageShape<BO, RO, NT>::PER][RO],
                                               const F& fin) {
     constexpr int RI = next_radix(W / NSI);
     using SI = StageShape<BI, RI, NT>;
     float2 u[SI::PER][RI];
-    put_part<BO, RO, NSO, NT, false>(lds, tid, v);
-    __syncthreads();
-    get_part<BI, RI, NT, false>(lds, tid, u);
-    __syncthreads();
-    put_part<BO, RO, NSO, NT, true>(lds, tid, v);
-    __syncthreads();
-    get_part<BI, RI, NT, true>(lds, tid, u);
+    if constexpr (WHOLE) {
+      put_part<BO, RO, NSO, NT, Part::kWhole>(lds, tid, v);
+      __syncthreads();
+      get_part<BI, RI, NT, Part::kWhole>(lds, tid, u);
+    } else {
+      put_part<BO, RO, NSO, NT, Part::kRe>(lds, tid, v);
+      __syncthreads();
+      get_part<BI, RI, NT, Part::kRe>(lds, tid, u);
+      __syncthreads();
+      put_part<BO, RO, NSO, NT, Part::kIm>(lds, tid, v);
+      __syncthreads();
+      get_part<BI, RI, NT, Part::kIm>(lds, tid, u);
+    }
     if constexpr (NSI > 1) {
 #pragma unroll
       for (int p = 0; p < SI::PER; ++p) {
@@ -466,22 +499,25 @@ __host__ __device__ constexpr int last_span(int w, int ns = 1) {
 // per window; window p belongs to the segment whose range holds it (its own
 // outputs and, for the sums, its own pixel lists).
 //
-// Bin sums: the squares of the real parts, then of the imaginary parts (each
-// in LDS in turn) are summed over the lists. The lists are cut into chunks of
-// kWdListChunk = 64 entries (one per lane, kNoPix padding at the end of each
-// bin); chunk k belongs to the bin j with off[j] <= k < off[j + 1]. Wave w
-// takes the contiguous chunks [K w / NW, K (w + 1) / NW) of the K in all, so
-// it meets only a few bins: each lane sums its entry of the wave's chunks of a
-// bin in order, one wave sum per bin met and component is added to red[j][w]
-// (zero for the bins a wave does not meet), and the bin total adds red[j][0 ..
-// NW) in order. The pixel indices of kWdChunks chunks are loaded together, so
-// the load latency is paid once per group of chunks.
+// Bin sums: |Psi|^2 (where the window passes through LDS by components: the
+// squares of the real parts, then of the imaginary parts) is summed over the
+// lists. The lists are cut into chunks of kWdListChunk = 64 entries (one per
+// lane, kNoPix padding at the end of each bin); chunk k belongs to the bin j
+// with off[j] <= k < off[j + 1]. Wave w takes the contiguous chunks [K w / NW,
+// K (w + 1) / NW) of the K in all, so it meets only a few bins: each lane sums
+// its entry of the wave's chunks of a bin in order, one wave sum per bin met
+// and walk is added to red[j][w] (zero for the bins a wave does not meet), and
+// the bin total adds red[j][0 .. NW) in order. The pixel indices of kWdChunks
+// chunks are loaded together, so the load latency is paid once per group of
+// chunks. Bound: the exchanges and these sums, whose VALU work alone is 8 us
+// per window of W = 128 and compute unit where the loads take 6.
 template <int W, bool CBED>
 __global__ __launch_bounds__(wd_nt(W)) __attribute__((amdgpu_waves_per_eu(wd_wpe(W))))
 void k_window_detect(const float2* __restrict__ window,
                                                             const float2* __restrict__ twW,
                                                             const WindowSegs segs) {
-  using WF = WinFft<W>;
+  constexpr bool WHOLE = wd_whole(W, CBED);
+  using WF = WinFft<W, WHOLE>;
   using Rows = typename WF::Rows;
   using Cols = typename WF::Cols;
   constexpr int NT = WF::NT;
@@ -489,7 +525,7 @@ void k_window_detect(const float2* __restrict__ window,
   constexpr int R0 = next_radix(W), NSL = last_span(W), RL = W / NSL;
   using S0 = StageShape<Rows, R0, NT>;
   using SL = StageShape<Cols, RL, NT>;
-  __shared__ float lds[fl_padded(W * W)];
+  __shared__ typename WF::T lds[WF::SIZE];
   __shared__ float2 tw[W];
   __shared__ double red[CBED ? 1 : kMaxDet][NW];
   const int tid = threadIdx.x;
@@ -559,8 +595,11 @@ void k_window_detect(const float2* __restrict__ window,
                 while (kk >= off[j + 1]);
               }
               const bool ok = px[c] != (int)kNoPix;
-              const double x = (double)lds[flpad(ok ? px[c] : 0)];
-              acc += ok ? x * x : 0.0;
+              const auto z = lds[padded<WF::Lds::SH>(ok ? px[c] : 0)];
+              double I;
+              if constexpr (WHOLE) I = (double)z.x * z.x + (double)z.y * z.y;
+              else I = (double)z * z;
+              acc += ok ? I : 0.0;
             }
           }
         }
@@ -569,13 +608,19 @@ void k_window_detect(const float2* __restrict__ window,
           if (lane == 0) red[j][wv] += sm;
         }
       };
-      put_part<Cols, RL, NSL, NT, false>(lds, tid, z);
-      __syncthreads();
-      sum_part();
-      __syncthreads();
-      put_part<Cols, RL, NSL, NT, true>(lds, tid, z);
-      __syncthreads();
-      sum_part();
+      if constexpr (WHOLE) {
+        put_part<Cols, RL, NSL, NT, Part::kWhole>(lds, tid, z);
+        __syncthreads();
+        sum_part();
+      } else {
+        put_part<Cols, RL, NSL, NT, Part::kRe>(lds, tid, z);
+        __syncthreads();
+        sum_part();
+        __syncthreads();
+        put_part<Cols, RL, NSL, NT, Part::kIm>(lds, tid, z);
+        __syncthreads();
+        sum_part();
+      }
       __syncthreads();
       if (tid < nb) {
         double sm = 0.0;
