@@ -115,11 +115,6 @@ struct ActiveBeam {
   int m, n;   // plane-wave indices
 };
 
-// Workgroups per probe group along the union tiles (each loops over tiles):
-// the tiles of one window / window_tile_div, more where the launch's groups
-// are too few to fill the GPU with that.
-int contract_tile_slots(int w, int window_tile_div, int groups);
-
 // Low-precision probe step (BF16 or FP16 operands, FP32 accumulation).
 // Operand forms of the packed window sum: 16-bit (BF16, FP16; one 32-bit
 // word per complex value, 32 beams per K block) or FP32 (two words per
@@ -128,6 +123,10 @@ enum class Prec { kBF16 = 1, kFP16 = 2, kF32 = 3 };
 // Probes per group of the packed window sum (they share one union window):
 // the default for window side w and the operand type.
 int contract_group(int w, Prec pr);
+// Workgroups per probe group along the union tiles (each loops over tiles):
+// the tiles of one window / window_tile_div, more where the launch's groups
+// are too few to fill the GPU with that.
+int contract_tile_slots(int w, int window_tile_div, int groups, int group, Prec pr);
 constexpr int kC16KB = 32;  // 32-bit words per K block row
 __host__ __device__ constexpr int prec_block_beams(Prec p) { return p == Prec::kF32 ? 16 : 32; }
 __host__ __device__ constexpr int prec_words(Prec p) { return p == Prec::kF32 ? 2 : 1; }

@@ -823,7 +823,7 @@ hipError_t launch_alpha16(const double* probe_xy, int p0, int np, const ActiveBe
 hipError_t launch_contract16(const ContractSegs& segs, int w, int group, Prec prec,
                              int window_tile_div, hipStream_t st) {
   if (segs.n < 1 || segs.n > kMaxSeg || segs.groups < 1) return hipErrorInvalidValue;
-  const int slots = contract_tile_slots(w, window_tile_div, segs.groups);
+  const int slots = contract_tile_slots(w, window_tile_div, segs.groups, group, prec);
   int set = segs.groups >= 128 ? 4 : 0;
   const int wgs = set == 0 ? slots * segs.groups
                            : ((segs.groups + set - 1) / set + 7) / 8 * 8 * set * slots;

@@ -20,13 +20,6 @@ namespace {
 // per group for W >= 128, and the union tiles of 128 pixels.
 constexpr int kCG128 = 64;
 constexpr int kCTile = 128;
-// Workgroups a window-sum launch has at least: four rounds of the 512 that are
-// resident, so that groups of unequal unions even out. With the tuned slots
-// alone, one group of 15 probes (W = 128) ran on 16 workgroups (199 us, now
-// 30) and 89 ragged groups (W = 64) on 356 (787 us, now 386). More than the
-// tiles of two windows per group are never needed by windows that overlap.
-constexpr int kCSlots = 2048;
-
 // ---------------------------------------------------------------------------
 // W = 256 windows (too large for one workgroup's LDS): the 2D FFT runs as
 // two four-step passes over the window buffer, 256 = 16 x 16.
@@ -649,10 +642,27 @@ int contract_group(int w, Prec pr) {
   return w >= 128 ? kCG128 : (w >= 64 ? 32 : 16);
 }
 
-int contract_tile_slots(int w, int window_tile_div, int groups) {
+// A launch has at least kCFill workgroups, so that groups of unequal unions even
+// out: with own / 4 slots one group of 15 probes of W = 128 ran on 32 workgroups
+// (164 us, on 256 39) and the 38 groups of 1200 scattered probes of W = 64 on 304
+// (193 us, on 2280 110). FP32 groups of 16 and 32 probes leave registers and LDS
+// for three workgroups per compute unit, and their launches have three whole
+// rounds of those 768. Rounds that end part full, and slots in powers of two,
+// which put the tiles beyond a whole number per slot on the same compute units
+// in every group, cost aligned scans up to a quarter (W = 64: 2048 probes 166 us
+// with 2048 workgroups, 127 with 2304; 1024 probes 98 and 69; a ragged scan of
+// 5673 probes 403 and 392; over 108 scans 0.5 % on average, the worst 8 % longer).
+// 16-bit sums and groups of 64 are on average as fast or faster with 2048, a
+// multiple of which keeps one tile of neighbouring groups on one XCD. More than
+// the tiles of two windows per group are never needed by windows that overlap.
+constexpr int kCFill = 2048, kCFill32 = 3 * 768;
+
+int contract_tile_slots(int w, int window_tile_div, int groups, int group, Prec pr) {
   const int own = (w * w + kCTile - 1) / kCTile;  // tiles of one window
   const int want = std::max(1, own / std::max(1, window_tile_div));
-  return std::max(want, std::min(2 * own, (kCSlots + groups - 1) / groups));
+  const int fill = pr == Prec::kF32 && group < 64 ? kCFill32 / groups
+                                                  : (kCFill + groups - 1) / groups;
+  return std::max(want, std::min(2 * own, fill));
 }
 
 int window_big_tiles(int w) { return w / 16; }

@@ -100,7 +100,7 @@ hipError_t launch_reduce_partials(const double*, int, int, int, double*, OutAcc,
 hipError_t launch_extract(const float2*, int, int, float2*, const float2*, hipStream_t st) {
   return launch(st);
 }
-int contract_tile_slots(int, int, int) { return 1; }
+int contract_tile_slots(int, int, int, int, Prec) { return 1; }
 int contract_group(int, Prec) { return 16; }
 hipError_t launch_s16_scale(const float2*, const ActiveBeam*, int, int, float*, float*,
                             hipStream_t st) {
