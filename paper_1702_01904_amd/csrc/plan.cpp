@@ -339,7 +339,6 @@ const prism_plan::PixLists* get_pixlists(prism_plan* p, int w, int f, const pris
 // ---------------------------------------------------------------- layouts
 
 constexpr size_t kChunkBytes = size_t(1) << 30;  // preferred probe-window bytes per chunk
-constexpr int kSelectProbes = 2048;  // most probes of a fill that packs only what its windows meet
 
 size_t state_bytes(int n) { return (size_t)n * (n / 2) * sizeof(float2); }
 
@@ -401,6 +400,21 @@ int group_of(const prism_plan* p, int w) {
 // shrinks (the same results, fewer probes per union window), a set one stays
 int least_group(const prism_plan* p, int w) {
   return p->probe_group > 0 ? p->probe_group : std::min(16, group_of(p, w));
+}
+
+// Whether a fill of `probes` probes packs only the pixel tiles that its windows
+// meet. Every workgroup of a tile tests the windows, 256 at a time, before its
+// first load, so the copy that may be saved has to outweigh the tests: the full
+// pack moves at least 24 MiB, more with more probes, and there are at most 2048.
+// Measured (full pack / selective with windows near each other / selective with
+// every tile met, us): 29 beams on 256^2 (30 MiB), 63 probes 8.9 / 6.7 / 13.6
+// (full with the same probes 12.7); 121 beams on 256^2 (124 MiB), 247 probes 24.3
+// / 14.1 / 24.2, 1998 probes 23.6 / 19.6 / 25.8; 481 beams on 512^2 (1.9 GiB), 12
+// probes 417 / 93, 1998 probes 400 / 160 / 419. Below the line: 29 beams on 128^2
+// (8 MiB), 1998 probes 7.5 / 10.8 / 11.0.
+bool pack_select(int n_act, int n_actp, int ns, prism::Prec pk, int probes) {
+  const double mib = (double)ns * ns * (8.0 * n_act + 4.0 * prism::prec_words(pk) * n_actp) / (1 << 20);
+  return probes <= 2048 && mib >= 24.0 + probes * (3.0 / 64);
 }
 
 // Active beams padded to whole K blocks.
@@ -692,18 +706,14 @@ int run_sub(std::vector<Req>& rq, const Sub& sb, int chunk, void* base, hipStrea
   }
   // The S-matrices are packed at the first flush, after its coefficient
   // launches: those give the window origins, and where the flush holds every
-  // probe of this fill and they are few (kSelectProbes), only the pixel tiles
-  // that a window meets are packed. Each tile's workgroups test every window,
-  // 256 at a time, so the test stays below the copy it may save: with 15
-  // probes of 128^2 windows on a 512^2 S-matrix (305 beams) the pack takes
-  // 53 us instead of 300, with 1024 scattered 256^2 windows on 1024^2
-  // (289 beams, BF16) 700 instead of 990.
+  // probe of this fill, only the pixel tiles that a window meets are packed if
+  // that can pay (pack_select).
   bool packed = false;
   auto pack_all = [&](int probes) -> int {
     packed = true;
-    const bool select = probes == sb.probes && probes <= kSelectProbes;
     for (size_t k = 0; k < sb.packs.size(); ++k) {
       const Req& r = rq[sb.packs[k]];
+      const bool select = probes == sb.probes && pack_select(r.n_act, r.n_actp, r.ns, pr, probes);
       const PackWs& pw = bw.packs[k];
       // origins lie in [0, ns) of their own S-matrix: with several sizes in
       // one fill everything is packed

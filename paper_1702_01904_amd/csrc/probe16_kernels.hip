@@ -30,6 +30,8 @@
 //    (global_load_lds_dwordx4), one block ahead, which frees the staging
 //    registers for reading both K steps' operands before their products.
 //  * The 1 / (W sqrt(B_A)) normalisation is applied in FP32 at the end.
+#include <algorithm>
+
 #include "fft_lds.hpp"
 #include "kernels.hpp"
 
@@ -785,9 +787,16 @@ hipError_t launch_s16_pack(const float2* smatrix, const ActiveBeam* act, int n_a
                            int ns, const float* scale, const int2* org, int np, int w, void* s16,
                            Prec prec, hipStream_t st) {
   const int nblk = n_actp / prec_block_beams(prec);
-  // the workgroups of a tile that packs selectively repeat its window test:
-  // a quarter as many, each walking up to four beam blocks
-  const dim3 grid((unsigned)((size_t)ns * ns / 64), (unsigned)(org ? (nblk + 3) / 4 : nblk));
+  const int tiles = ns * ns / 64;
+  // The workgroups of a tile that packs selectively repeat its window test, so
+  // each walks more beam blocks the longer that test is (4, 2 per 256 probes),
+  // as long as 4096 workgroups are left to find the tiles that are met.
+  int gy = nblk;
+  if (org) {
+    const int walk = std::max(4, 2 * ((np + 255) / 256));
+    gy = std::max((nblk + walk - 1) / walk, std::min(nblk, (4096 + tiles - 1) / tiles));
+  }
+  const dim3 grid((unsigned)tiles, (unsigned)gy);
   if (prec == Prec::kF32) {
     hipLaunchKernelGGL(k_s32_pack, grid, dim3(256), 0, st, smatrix, act, n_act, n_actp, ns, org,
                        np, w, static_cast<float2*>(s16));
