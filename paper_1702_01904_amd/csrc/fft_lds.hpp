@@ -72,21 +72,37 @@ __host__ __device__ __forceinline__ void dft4(float2 (&v)[4]) {
   dft4v<INV>(v[0], v[1], v[2], v[3]);
 }
 
+// x sqrt(1/2) and x sqrt(3/4). The nearest floats are 1.7e-8 below these
+// numbers, which takes 2 to 3e-7 of the intensity per slice from a wave that
+// goes through several such products in each of its four transforms. EX adds the
+// rest of the constant (one more product).
+template <bool EX>
+__host__ __device__ __forceinline__ float mul_sqrt12(float x) {
+  constexpr float r = 0.70710678118654752440f;
+  if constexpr (EX) return __builtin_fmaf(x, r, x * (float)(0.70710678118654752440 - (double)r));
+  else return r * x;
+}
+template <bool EX>
+__host__ __device__ __forceinline__ float mul_sqrt34(float x) {
+  constexpr float h = 0.86602540378443864676f;
+  if constexpr (EX) return __builtin_fmaf(x, h, x * (float)(0.86602540378443864676 - (double)h));
+  else return h * x;
+}
+
 // 8-point DFT as two 4-point DFTs (even/odd inputs) and a twiddled merge.
-template <bool INV>
+template <bool INV, bool EX = false>
 __host__ __device__ __forceinline__ void dft8(float2 (&v)[8]) {
   float2 e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6];
   float2 o0 = v[1], o1 = v[3], o2 = v[5], o3 = v[7];
   dft4v<INV>(e0, e1, e2, e3);
   dft4v<INV>(o0, o1, o2, o3);
-  const float r = 0.70710678118654752440f;
   // o1 *= w^1, o2 *= w^2, o3 *= w^3 with w = exp(-+ 2 pi i / 8)
   if (INV) {
-    o1 = make_float2(r * (o1.x - o1.y), r * (o1.x + o1.y));
-    o3 = make_float2(-r * (o3.x + o3.y), r * (o3.x - o3.y));
+    o1 = make_float2(mul_sqrt12<EX>(o1.x - o1.y), mul_sqrt12<EX>(o1.x + o1.y));
+    o3 = make_float2(-mul_sqrt12<EX>(o3.x + o3.y), mul_sqrt12<EX>(o3.x - o3.y));
   } else {
-    o1 = make_float2(r * (o1.x + o1.y), r * (o1.y - o1.x));
-    o3 = make_float2(r * (o3.y - o3.x), -r * (o3.x + o3.y));
+    o1 = make_float2(mul_sqrt12<EX>(o1.x + o1.y), mul_sqrt12<EX>(o1.y - o1.x));
+    o3 = make_float2(mul_sqrt12<EX>(o3.y - o3.x), -mul_sqrt12<EX>(o3.x + o3.y));
   }
   o2 = mul_mi<INV>(o2);
   v[0] = cadd(e0, o0);
@@ -100,20 +116,19 @@ __host__ __device__ __forceinline__ void dft8(float2 (&v)[8]) {
 }
 
 // 3-point DFT: X1, X2 = a - (b + c)/2 -+ i (sqrt(3)/2)(b - c) (forward).
-template <bool INV>
+template <bool INV, bool EX = false>
 __host__ __device__ __forceinline__ void dft3v(float2& a, float2& b, float2& c) {
-  constexpr float h = 0.86602540378443864676f;  // sqrt(3) / 2
   const float2 t1 = cadd(b, c), t2 = csub(b, c);
   const float2 m = make_float2(a.x - 0.5f * t1.x, a.y - 0.5f * t1.y);
-  const float2 r = mul_mi<INV>(make_float2(h * t2.x, h * t2.y));  // -+ i h (b - c)
+  const float2 r = mul_mi<INV>(make_float2(mul_sqrt34<EX>(t2.x), mul_sqrt34<EX>(t2.y)));  // -+ i h (b - c)
   a = cadd(a, t1);
   b = cadd(m, r);
   c = csub(m, r);
 }
 
-template <bool INV>
+template <bool INV, bool EX = false>
 __host__ __device__ __forceinline__ void dft3(float2 (&v)[3]) {
-  dft3v<INV>(v[0], v[1], v[2]);
+  dft3v<INV, EX>(v[0], v[1], v[2]);
 }
 
 // cos and sin of 2 pi m / 12 for any integer m.
@@ -181,7 +196,7 @@ __host__ __device__ __forceinline__ float2 rot36(float2 a, int m) {
 }
 
 // 9-point DFT as 3 x 3 and 18-point as 2 x 9 (Cooley-Tukey, x = R2 a + b).
-template <int R1, int R2, bool INV>
+template <int R1, int R2, bool INV, bool EX = false>
 __host__ __device__ __forceinline__ void dft_ct36(float2 (&v)[R1 * R2]) {
   constexpr int R = R1 * R2;
   float2 y[R2][R1];
@@ -190,7 +205,7 @@ __host__ __device__ __forceinline__ void dft_ct36(float2 (&v)[R1 * R2]) {
 #pragma unroll
     for (int a = 0; a < R1; ++a) y[b][a] = v[R2 * a + b];
     if constexpr (R1 == 2) dft2<INV>(y[b]);
-    else dft3<INV>(y[b]);
+    else dft3<INV, EX>(y[b]);
 #pragma unroll
     for (int c = 1; c < R1; ++c) y[b][c] = rot36<INV>(y[b][c], (36 / R) * b * c);
   }
@@ -199,8 +214,8 @@ __host__ __device__ __forceinline__ void dft_ct36(float2 (&v)[R1 * R2]) {
     float2 z[R2];
 #pragma unroll
     for (int b = 0; b < R2; ++b) z[b] = y[b][c];
-    if constexpr (R2 == 3) dft3<INV>(z);
-    else dft_ct36<3, 3, INV>(z);
+    if constexpr (R2 == 3) dft3<INV, EX>(z);
+    else dft_ct36<3, 3, INV, EX>(z);
 #pragma unroll
     for (int d = 0; d < R2; ++d) v[c + R1 * d] = z[d];
   }
@@ -208,7 +223,7 @@ __host__ __device__ __forceinline__ void dft_ct36(float2 (&v)[R1 * R2]) {
 
 // R = R1 * R2 (6 = 2 * 3, 12 = 4 * 3): R2 DFTs of length R1 over a
 // (x = R2 a + b), twiddles w_R^{bc}, R1 DFTs of length R2 over b.
-template <int R1, int R2, bool INV>
+template <int R1, int R2, bool INV, bool EX = false>
 __host__ __device__ __forceinline__ void dft_ct12(float2 (&v)[R1 * R2]) {
   constexpr int R = R1 * R2;
   float2 y[R2][R1];
@@ -226,24 +241,24 @@ __host__ __device__ __forceinline__ void dft_ct12(float2 (&v)[R1 * R2]) {
     float2 z[R2];
 #pragma unroll
     for (int b = 0; b < R2; ++b) z[b] = y[b][c];
-    dft3<INV>(z);
+    dft3<INV, EX>(z);
 #pragma unroll
     for (int d = 0; d < R2; ++d) v[c + R1 * d] = z[d];
   }
 }
 
-template <int R, bool INV>
+template <int R, bool INV, bool EX = false>
 __host__ __device__ __forceinline__ void dft(float2 (&v)[R]) {
   static_assert(R == 2 || R == 3 || R == 4 || R == 6 || R == 8 || R == 9 || R == 12 || R == 18,
                 "register DFT lengths 2, 3, 4, 6, 8, 9, 12, 18");
   if constexpr (R == 2) dft2<INV>(v);
-  else if constexpr (R == 3) dft3<INV>(v);
+  else if constexpr (R == 3) dft3<INV, EX>(v);
   else if constexpr (R == 4) dft4<INV>(v);
-  else if constexpr (R == 6) dft_ct12<2, 3, INV>(v);
-  else if constexpr (R == 12) dft_ct12<4, 3, INV>(v);
-  else if constexpr (R == 9) dft_ct36<3, 3, INV>(v);
-  else if constexpr (R == 18) dft_ct36<2, 9, INV>(v);
-  else dft8<INV>(v);
+  else if constexpr (R == 6) dft_ct12<2, 3, INV, EX>(v);
+  else if constexpr (R == 12) dft_ct12<4, 3, INV, EX>(v);
+  else if constexpr (R == 9) dft_ct36<3, 3, INV, EX>(v);
+  else if constexpr (R == 18) dft_ct36<2, 9, INV, EX>(v);
+  else dft8<INV, EX>(v);
 }
 
 // Batch geometry of LDS-held sequences (see header comment).
@@ -281,7 +296,9 @@ __device__ __forceinline__ void stage_coords(int b, int& s, int& j) {
 // already applied), split into its two halves so that callers can keep a
 // stage's inputs or outputs in registers:
 //   stage_in  reads the R inputs of each butterfly of this thread from LDS
-//             and applies the twiddles (none when NS == 1);
+//             and applies the twiddles (none when NS == 1): w, w^2 and w^4 from
+//             the table and the other powers as products of two of them, or
+//             (EX) every power from the table, which rounds less;
 //   stage_out applies the R-point DFTs and writes the outputs to LDS.
 // Butterfly j of sequence s reads elements j + r L/R and writes elements
 // (j - k) R + k + r NS with k = j mod NS. tw: exp(-2 pi i m / L), m < L.
@@ -304,7 +321,7 @@ __device__ __forceinline__ int lpad_step(int base_padded, int base, int r) {
   }
 }
 
-template <class B, int R, int NS, int NT, bool INV>
+template <class B, int R, int NS, int NT, bool INV, bool EX = false>
 __device__ __forceinline__ void stage_in(const float2* lds, const float2* tw, int tid,
                                          float2 (&v)[StageShape<B, R, NT>::PER][R]) {
   using SS = StageShape<B, R, NT>;
@@ -322,13 +339,10 @@ __device__ __forceinline__ void stage_in(const float2* lds, const float2* tw, in
 #pragma unroll
       for (int r = 0; r < R; ++r) v[p][r] = lds[lpad_step<STEP>(pbase, base, r)];
       if constexpr (NS > 1) {
-        // twiddles w^r, w = exp(-+2 pi i k / (NS R)): w, w^2, w^4 from the
-        // table, the other powers as products. The row pass is bound by LDS
-        // traffic; this trades 4 of 7 table reads for complex products (the
-        // FP32 path's error roughly doubles, ~1.7e-5 relative at 1024^2 and
-        // 50 slices).
+        // twiddles w^r, w = exp(-+2 pi i k / (NS R)); products in place of
+        // table reads save LDS reads (4 of 7 in radix 8)
         float2 w[R];
-        if constexpr (R == 2 || R == 4 || R == 8) {
+        if constexpr (!EX && (R == 2 || R == 4 || R == 8)) {
           w[1] = tw[k * TWS];
           if constexpr (R >= 4) w[2] = tw[2 * k * TWS];
           if constexpr (R == 4) w[3] = cmul(w[1], w[2]);
@@ -339,7 +353,7 @@ __device__ __forceinline__ void stage_in(const float2* lds, const float2* tw, in
             w[6] = cmul(w[2], w[4]);
             w[7] = cmul(w[3], w[4]);
           }
-        } else {  // radix 3, 6, 9, 12, 18: every power from the table
+        } else {
 #pragma unroll
           for (int r = 1; r < R; ++r) w[r] = tw[r * k * TWS];
         }
@@ -350,7 +364,7 @@ __device__ __forceinline__ void stage_in(const float2* lds, const float2* tw, in
   }
 }
 
-template <class B, int R, int NS, int NT, bool INV>
+template <class B, int R, int NS, int NT, bool INV, bool EX = false>
 __device__ __forceinline__ void stage_out(float2* lds, int tid,
                                           float2 (&v)[StageShape<B, R, NT>::PER][R]) {
   using SS = StageShape<B, R, NT>;
@@ -360,7 +374,7 @@ __device__ __forceinline__ void stage_out(float2* lds, int tid,
     if (!SS::GUARD || b < SS::TOT) {
       int s, j;
       stage_coords<B, SS::NB>(b, s, j);
-      dft<R, INV>(v[p]);
+      dft<R, INV, EX>(v[p]);
       const int k = j % NS;
       const int o = (j - k) * R + k;
       constexpr int STEP = NS * B::ESTR;
@@ -373,21 +387,21 @@ __device__ __forceinline__ void stage_out(float2* lds, int tid,
 }
 
 // One complete in-place stage (read, barrier, write, barrier).
-template <class B, int R, int NS, int NT, bool INV>
+template <class B, int R, int NS, int NT, bool INV, bool EX = false>
 __device__ __forceinline__ void fft_stage(float2* lds, const float2* tw, int tid) {
   float2 v[StageShape<B, R, NT>::PER][R];
-  stage_in<B, R, NS, NT, INV>(lds, tw, tid, v);
+  stage_in<B, R, NS, NT, INV, EX>(lds, tw, tid, v);
   __syncthreads();
-  stage_out<B, R, NS, NT, INV>(lds, tid, v);
+  stage_out<B, R, NS, NT, INV, EX>(lds, tid, v);
   __syncthreads();
 }
 
 // COUNT consecutive radix-8 stages starting at span NS.
-template <class B, int NT, bool INV, int NS, int COUNT>
+template <class B, int NT, bool INV, int NS, int COUNT, bool EX = false>
 __device__ __forceinline__ void fft_radix8_run(float2* lds, const float2* tw, int tid) {
   if constexpr (COUNT > 0) {
-    fft_stage<B, 8, NS, NT, INV>(lds, tw, tid);
-    fft_radix8_run<B, NT, INV, NS * 8, COUNT - 1>(lds, tw, tid);
+    fft_stage<B, 8, NS, NT, INV, EX>(lds, tw, tid);
+    fft_radix8_run<B, NT, INV, NS * 8, COUNT - 1, EX>(lds, tw, tid);
   }
 }
 

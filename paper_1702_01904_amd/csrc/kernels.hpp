@@ -86,6 +86,10 @@ hipError_t launch_probe_init(float2* state, const double* probe_xy, int p0, int 
 int four_step_radix(int n);
 // tw2[m][j] = exp(-2 pi i j m / n), j, m < R (n entries; nothing for R = 0).
 hipError_t launch_twiddles2(float2* tw2, int n, hipStream_t st);
+// Whether a call of so many waves runs faster on the LDS passes (few = true
+// below; not with init or wtrans). Decided for a whole call, so that its results
+// do not depend on how a workspace cuts it into launches.
+bool few_waves(int n, int nwaves);
 // init != nullptr: first slice of a build, the state is only written (its
 // inputs are the beams' plane waves).
 // wtrans != nullptr: wave w multiplies by wtrans[w] + soff instead of trans_p
@@ -94,10 +98,11 @@ hipError_t launch_twiddles2(float2* tw2, int n, hipStream_t st);
 hipError_t launch_row_pass(float2* state, int nwaves, int n, const float2* trans_p,
                            const float2* twN, const float2* tw2, const LaunchTuning& tune,
                            hipStream_t st, const BeamWaves* init = nullptr,
-                           const float2* const* wtrans = nullptr, size_t soff = 0);
+                           const float2* const* wtrans = nullptr, size_t soff = 0,
+                           bool few = false);
 hipError_t launch_col_pass(float2* state, int nwaves, int n, const float2* prop_p,
                            const float2* twN, const float2* tw2, const LaunchTuning& tune,
-                           hipStream_t st);
+                           hipStream_t st, bool few = false);
 // Last slice of multislice STEM: FFT_y, propagator, band limit, |Psi|^2/n^2
 // and per-column-tile detector partial sums (double [wave][tiles][n_det]).
 hipError_t launch_col_detect(const float2* state, int nwaves, int n, const float2* prop_p,

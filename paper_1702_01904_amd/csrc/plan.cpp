@@ -919,13 +919,18 @@ int multislice_step(prism_plan* p, const double* xy, int P, const prism_optics* 
                          st),
           "copy aperture rows");
   const int tiles = prism::col_tiles(n);
+  const bool few = prism::few_waves(n, P);
   for (int p0 = 0; p0 < P; p0 += chunk) {
     const int np = std::min(chunk, P - p0);
     LAUNCH(p, st, "probe_init", prism::launch_probe_init(w.state, xy, p0, np, n, po, w.aper, w.twN, st));
     for (int s = 0; s < p->H; ++s) {
-      LAUNCH(p, st, "row_pass", prism::launch_row_pass(w.state, np, n, w.trans + (size_t)s * n * n, w.twN, w.tw2, p->tune, st));
+      LAUNCH(p, st, "row_pass",
+             prism::launch_row_pass(w.state, np, n, w.trans + (size_t)s * n * n, w.twN, w.tw2,
+                                    p->tune, st, nullptr, nullptr, 0, few));
       if (s + 1 < p->H) {
-        LAUNCH(p, st, "col_pass", prism::launch_col_pass(w.state, np, n, w.prop + (size_t)s * n, w.twN, w.tw2, p->tune, st));
+        LAUNCH(p, st, "col_pass",
+               prism::launch_col_pass(w.state, np, n, w.prop + (size_t)s * n, w.twN, w.tw2, p->tune,
+                                      st, few));
       } else {
         LAUNCH(p, st, "col_detect", prism::launch_col_detect(w.state, np, n, w.prop + (size_t)s * n, w.twN, bins,
                                          w.partial, st));

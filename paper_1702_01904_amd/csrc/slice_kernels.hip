@@ -21,7 +21,10 @@ namespace {
 
 // Launch shapes (tuned on MI355X; overridable at build time).
 #ifndef PRISM_COL_E
-#define PRISM_COL_E 8          // complex values per detector column-pass thread
+#define PRISM_COL_E 8          // complex values per LDS column-pass thread
+#endif
+#ifndef PRISM_ROW_ELEMS
+#define PRISM_ROW_ELEMS 2048   // complex values per LDS row-pass workgroup
 #endif
 
 // Largest power of two p with p n <= cap (at least 1): rows per workgroup
@@ -35,6 +38,8 @@ __host__ __device__ constexpr int col_nt(int n) {
              ? 64
              : (col_tc(n) * n / PRISM_COL_E > 1024 ? 1024 : col_tc(n) * n / PRISM_COL_E);
 }
+constexpr int kRowNT = PRISM_ROW_ELEMS / 8;
+__host__ __device__ constexpr int row_nseq(int n) { return pow2_rows(n, PRISM_ROW_ELEMS); }
 __host__ __device__ constexpr int ext_nseq(int n) { return pow2_rows(n, 4096); }
 
 // Map launch order onto tiles so that consecutive tiles run on the same
@@ -545,16 +550,106 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_col_steps(float2* __restrict__ st
 }
 
 // ---------------------------------------------------------------------------
-// Last column pass of multislice over a tile of TC adjacent compact columns,
-// held [y][c] in LDS: the forward y-transform reads straight from HBM, its
-// last stage stays in registers for the propagator and band limit, then
-// I = |Psi|^2 / n^2 gives per-tile detector partial sums.
+// LDS passes: the row and column pass of few waves on the grids of k_row_steps /
+// k_col_steps (multislice of a few probes, few_waves), and the last column pass
+// of multislice on every grid. 8 values per thread: a single wave's pass is a
+// chain of short stages over many threads, where the step passes have 16 to 32
+// values per lane and a wave function gives them few workgroups (n = 512, one
+// wave: row pass 7 us instead of 12, column pass 9 instead of 13). Their
+// arithmetic is the exact form (EX) of fft_lds.hpp: with the products of table
+// twiddles and plain constants the detector sums' error is three times larger (n =
+// 768, 40 slices: 9.0e-6; exact 1.2e-6; step passes 5.2e-6).
+//
+// Row pass: NSEQ rows of length n per workgroup (PRISM_ROW_ELEMS complex in
+// LDS). The inverse x-transform runs 8, 8^MID, RL and the forward one
+// RL, 8^MID, 8 (PairedPlan): the inverse's first stage reads the compact row
+// straight from HBM (its inputs at |kx| >= n/4 are zero), its last stage
+// stays in registers, is multiplied by t_p / n and feeds the forward's first
+// stage, and the forward's last stage stores only the kept half band.
 template <int N>
-__global__ __launch_bounds__(col_nt(N)) void k_col_detect(const float2* __restrict__ state,
-                                                          const float2* __restrict__ prop,
-                                                          const float2* __restrict__ twN,
-                                                          DetBins bins,
-                                                          double* __restrict__ partial) {
+__global__ __launch_bounds__(kRowNT) void k_row_lds(float2* __restrict__ state,
+                                                    const float2* __restrict__ trans,
+                                                    const float2* __restrict__ twN) {
+  constexpr int NT = kRowNT;
+  constexpr int NSEQ = row_nseq(N);
+  constexpr int H2 = N / 2, E8 = N / 8;
+  using B = RowBatch<N, NSEQ>;
+  using PP = PairedPlan<N>;
+  constexpr int RL = PP::RL, NSL = N / PP::RL;
+  using S8 = StageShape<B, 8, NT>;
+  using SL = StageShape<B, RL, NT>;
+  __shared__ float2 lds[lds_padded(NSEQ * N)];
+  __shared__ float2 tw[N];
+  const int tid = threadIdx.x;
+  const size_t row0 = (size_t)blockIdx.x * NSEQ;
+  load_twiddles<N, NT>(tw, twN, tid);
+  {
+    // inverse, first stage (span 1): inputs j + r n/8, nonzero for r in {0,1,6,7}
+    float2 v[S8::PER][8];
+#pragma unroll
+    for (int p = 0; p < S8::PER; ++p) {
+      const int b = tid + p * NT;
+      v[p][2] = v[p][3] = v[p][4] = v[p][5] = make_float2(0.f, 0.f);
+      if (S8::GUARD && b >= S8::TOT) continue;  // no butterfly (stage_out skips it too)
+      int sq, j;
+      stage_coords<B, S8::NB>(b, sq, j);
+      const float2* src = state + (row0 + sq) * H2 + j;
+      v[p][0] = src[0];
+      v[p][1] = src[E8];
+      v[p][6] = src[2 * E8];
+      v[p][7] = src[3 * E8];
+    }
+    stage_out<B, 8, 1, NT, true, true>(lds, tid, v);
+  }
+  __syncthreads();
+  fft_radix8_run<B, NT, true, 8, PP::MID, true>(lds, tw, tid);
+  float2 v[SL::PER][RL];
+  stage_in<B, RL, NSL, NT, true, true>(lds, tw, tid, v);
+#pragma unroll
+  for (int p = 0; p < SL::PER; ++p) {
+    const int b = tid + p * NT;
+    if (SL::GUARD && b >= SL::TOT) continue;
+    int sq, j;
+    stage_coords<B, SL::NB>(b, sq, j);
+    dft<RL, true, true>(v[p]);
+    const float2* t = trans + (size_t)((row0 + sq) % (size_t)N) * N + j;
+#pragma unroll
+    for (int r = 0; r < RL; ++r) v[p][r] = cmul(v[p][r], t[r * NSL]);
+  }
+  __syncthreads();
+  stage_out<B, RL, 1, NT, false, true>(lds, tid, v);
+  __syncthreads();
+  fft_radix8_run<B, NT, false, RL, PP::MID, true>(lds, tw, tid);
+  {
+    // forward, last stage (span n/8): outputs j + r n/8, kept for r in {0,1,6,7}
+    float2 w[S8::PER][8];
+    stage_in<B, 8, E8, NT, false, true>(lds, tw, tid, w);
+#pragma unroll
+    for (int p = 0; p < S8::PER; ++p) {
+      const int b = tid + p * NT;
+      if (S8::GUARD && b >= S8::TOT) continue;
+      int sq, j;
+      stage_coords<B, S8::NB>(b, sq, j);
+      dft8<false, true>(w[p]);
+      float2* dst = state + (row0 + sq) * H2 + j;
+      dst[0] = w[p][0];
+      dst[E8] = w[p][1];
+      dst[2 * E8] = w[p][6];
+      dst[3 * E8] = w[p][7];
+    }
+  }
+}
+
+// Column pass over a tile of TC adjacent compact columns, held [y][c] in LDS:
+// the forward y-transform reads straight from HBM, its last stage stays in
+// registers for the propagator and band limit and feeds the inverse, whose last
+// stage stores. DETECT (last slice of multislice): instead of the inverse, I =
+// |Psi|^2 / n^2 gives per-tile detector partial sums.
+template <int N, bool DETECT>
+__global__ __launch_bounds__(col_nt(N)) void k_col_lds(float2* __restrict__ state,
+                                                       const float2* __restrict__ prop,
+                                                       const float2* __restrict__ twN, DetBins bins,
+                                                       double* __restrict__ partial) {
   constexpr int TC = col_tc(N), NT = col_nt(N);
   constexpr int H2 = N / 2, Q = N / 4, E8 = N / 8;
   constexpr int TILES = H2 / TC;
@@ -569,7 +664,7 @@ __global__ __launch_bounds__(col_nt(N)) void k_col_detect(const float2* __restri
   const int tid = threadIdx.x;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int w = tile / TILES, c0 = (tile % TILES) * TC;
-  const float2* base = state + (size_t)w * N * H2 + c0;
+  float2* base = state + (size_t)w * N * H2 + c0;
   load_twiddles<N, NT>(tw, twN, tid);
   {
     float2 v[S8::PER][8];
@@ -582,19 +677,20 @@ __global__ __launch_bounds__(col_nt(N)) void k_col_detect(const float2* __restri
 #pragma unroll
       for (int r = 0; r < 8; ++r) v[p][r] = base[(size_t)(j + r * E8) * H2 + c];
     }
-    stage_out<B, 8, 1, NT, false>(lds, tid, v);
+    stage_out<B, 8, 1, NT, false, !DETECT>(lds, tid, v);
   }
   __syncthreads();
-  fft_radix8_run<B, NT, false, 8, PP::MID>(lds, tw, tid);
+  fft_radix8_run<B, NT, false, 8, PP::MID, !DETECT>(lds, tw, tid);
   float2 v[SL::PER][RL];
-  stage_in<B, RL, NSL, NT, false>(lds, tw, tid, v);
+  stage_in<B, RL, NSL, NT, false, !DETECT>(lds, tw, tid, v);
+  const float inv_n = 1.0f / (float)N;
 #pragma unroll
   for (int p = 0; p < SL::PER; ++p) {
     const int b = tid + p * NT;
     if (SL::GUARD && b >= SL::TOT) continue;
     int c, j;
     stage_coords<B, SL::NB>(b, c, j);
-    dft<RL, false>(v[p]);
+    dft<RL, false, !DETECT>(v[p]);
     const int jj = c0 + c;
     const int kx = jj < Q ? jj : jj - H2;
     const float2 px = prop[kx < 0 ? kx + N : kx];
@@ -604,50 +700,70 @@ __global__ __launch_bounds__(col_nt(N)) void k_col_detect(const float2* __restri
       const int ky = signed_k(yi, N);
       const int k2 = kx * kx + ky * ky;
       if (16 * k2 < N * N) {
-        v[p][r] = cmul(cmul(v[p][r], px), prop[yi]);
+        float2 z = cmul(cmul(v[p][r], px), prop[yi]);
+        v[p][r] = DETECT ? z : cscale(z, inv_n);
       } else {
         v[p][r] = make_float2(0.f, 0.f);
       }
     }
   }
-  __shared__ double red[8][NW];
-  const double inv_n2 = 1.0 / ((double)N * (double)N);
-  for (int j0 = 0; j0 < bins.n; j0 += 8) {
-    double acc[8];
+  if constexpr (!DETECT) {
+    __syncthreads();
+    stage_out<B, RL, 1, NT, true, true>(lds, tid, v);
+    __syncthreads();
+    fft_radix8_run<B, NT, true, RL, PP::MID, true>(lds, tw, tid);
+    float2 u[S8::PER][8];
+    stage_in<B, 8, E8, NT, true, true>(lds, tw, tid, u);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q] = 0.0;
-#pragma unroll
-    for (int p = 0; p < SL::PER; ++p) {
+    for (int p = 0; p < S8::PER; ++p) {
       const int b = tid + p * NT;
-      if (SL::GUARD && b >= SL::TOT) continue;
+      if (S8::GUARD && b >= S8::TOT) continue;
       int c, j;
-      stage_coords<B, SL::NB>(b, c, j);
-      const int jj = c0 + c;
-      const int kx = jj < Q ? jj : jj - H2;
+      stage_coords<B, S8::NB>(b, c, j);
+      dft8<true, true>(u[p]);
 #pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        const int ky = signed_k(j + r * NSL, N);
-        const int k2 = kx * kx + ky * ky;
-        const double I = ((double)v[p][r].x * v[p][r].x + (double)v[p][r].y * v[p][r].y) * inv_n2;
+      for (int r = 0; r < 8; ++r) base[(size_t)(j + r * E8) * H2 + c] = u[p][r];
+    }
+  } else {
+    __shared__ double red[8][NW];
+    const double inv_n2 = 1.0 / ((double)N * (double)N);
+    for (int j0 = 0; j0 < bins.n; j0 += 8) {
+      double acc[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int jb = j0 + q;
-          if (jb < bins.n && k2 >= bins.lo[jb] && k2 < bins.hi[jb]) acc[q] += I;
+      for (int q = 0; q < 8; ++q) acc[q] = 0.0;
+#pragma unroll
+      for (int p = 0; p < SL::PER; ++p) {
+        const int b = tid + p * NT;
+        if (SL::GUARD && b >= SL::TOT) continue;
+        int c, j;
+        stage_coords<B, SL::NB>(b, c, j);
+        const int jj = c0 + c;
+        const int kx = jj < Q ? jj : jj - H2;
+#pragma unroll
+        for (int r = 0; r < RL; ++r) {
+          const int ky = signed_k(j + r * NSL, N);
+          const int k2 = kx * kx + ky * ky;
+          const double I = ((double)v[p][r].x * v[p][r].x + (double)v[p][r].y * v[p][r].y) * inv_n2;
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            const int jb = j0 + q;
+            if (jb < bins.n && k2 >= bins.lo[jb] && k2 < bins.hi[jb]) acc[q] += I;
+          }
         }
       }
-    }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const double sum = wave_sum(acc[q]);
-      if ((tid & 63) == 0) red[q][tid >> 6] = sum;
+      for (int q = 0; q < 8; ++q) {
+        const double sum = wave_sum(acc[q]);
+        if ((tid & 63) == 0) red[q][tid >> 6] = sum;
+      }
+      __syncthreads();
+      if (tid < 8 && j0 + tid < bins.n) {
+        double sum = 0.0;
+        for (int wv = 0; wv < NW; ++wv) sum += red[tid][wv];
+        partial[((size_t)w * TILES + (tile % TILES)) * bins.n + j0 + tid] = sum;
+      }
+      __syncthreads();
     }
-    __syncthreads();
-    if (tid < 8 && j0 + tid < bins.n) {
-      double sum = 0.0;
-      for (int wv = 0; wv < NW; ++wv) sum += red[tid][wv];
-      partial[((size_t)w * TILES + (tile % TILES)) * bins.n + j0 + tid] = sum;
-    }
-    __syncthreads();
   }
 }
 
@@ -805,6 +921,20 @@ hipError_t launch_prop_lut(float2* lut, int n, int H, const double* thick_dev, d
     default: return hipErrorInvalidValue; \
   }
 
+// The grids of k_row_lds / k_col_lds<N, false> (few_waves).
+#define PRISM_DISPATCH_FEW(n, CALL) \
+  switch (n) {                      \
+    case 128: CALL(128); break;     \
+    case 192: CALL(192); break;     \
+    case 384: CALL(384); break;     \
+    case 512: CALL(512); break;     \
+    case 576: CALL(576); break;     \
+    case 768: CALL(768); break;     \
+    case 1152: CALL(1152); break;   \
+    case 1536: CALL(1536); break;   \
+    default: return hipErrorInvalidValue; \
+  }
+
 hipError_t launch_twiddles2(float2* tw2, int n, hipStream_t st) {
   const int R = four_step_radix(n);
   if (R == 0) return hipSuccess;
@@ -813,6 +943,23 @@ hipError_t launch_twiddles2(float2* tw2, int n, hipStream_t st) {
 }
 
 int four_step_radix(int n) { return n == 1024 ? 32 : (n == 256 ? 16 : 0); }
+
+// Most waves of a multislice call for which the LDS passes are faster than the
+// step passes of the same grid: the step passes' longer chain per lane is hidden
+// once a launch has about two workgroups per compute unit, sooner where their
+// rows are long and LDS tiles take most of a compute unit's LDS. Measured with 12
+// slices, step / LDS passes in us: n = 128, 8 probes 138 / 127, 48 probes 162 /
+// 162; n = 192, 8 probes 182 / 151, 96 probes 387 / 403; n = 384, 1 probe 234 /
+// 179, 64 probes 611 / 608; n = 512, 1 probe 266 / 180, 16 probes 477 / 440, 64
+// probes 794 / 856; n = 576, 1 probe 241 / 209, 8 probes 399 / 405; n = 768, 1
+// probe 322 / 247, 16 probes 700 / 660, 32 probes 1074 / 1137; n = 1152, 1 probe
+// 398 / 356, 4 probes 642 / 656; n = 1536, 1 probe 531 / 514, 2 probes 563 / 616;
+// n = 2048, 1 probe 741 / 744.
+bool few_waves(int n, int nwaves) {
+  const int most = n == 128 ? 32 : n == 192 ? 64 : n == 384 || n == 512 ? 48
+                 : n == 576 ? 6 : n == 768 ? 16 : n == 1152 ? 2 : n == 1536 ? 1 : 0;
+  return nwaves <= most;
+}
 
 // Workgroups of a slice-pass launch over `units` row groups or tiles: the 256
 // compute units times the workgroups one holds (per_cu), so that every
@@ -829,7 +976,7 @@ static unsigned pass_grid(int units, int per_cu, int maxit, int min_wgs) {
 hipError_t launch_row_pass(float2* state, int nwaves, int n, const float2* trans_p,
                            const float2* twN, const float2* tw2, const LaunchTuning& tune,
                            hipStream_t st, const BeamWaves* init, const float2* const* wtrans,
-                           size_t soff) {
+                           size_t soff, bool few) {
   const bool wt = wtrans != nullptr;
   const BeamWaves bw = init ? *init : BeamWaves{nullptr, 0, 0};
   if (init && wt) return hipErrorInvalidValue;  // first slices run one specimen at a time
@@ -854,6 +1001,15 @@ hipError_t launch_row_pass(float2* state, int nwaves, int n, const float2* trans
 #undef ROW4
     return hipGetLastError();
   }
+  if (few && (wt || init)) return hipErrorInvalidValue;  // multislice only
+  if (few) {
+#define ROWL(NN)                                                                               \
+  hipLaunchKernelGGL(k_row_lds<NN>, dim3((unsigned)((size_t)nwaves * NN / row_nseq(NN))),      \
+                     dim3(kRowNT), 0, st, state, trans_p, twN)
+    PRISM_DISPATCH_FEW(n, ROWL)
+#undef ROWL
+    return hipGetLastError();
+  }
 #define ROW1(NN, WW, II)                                                                        \
   hipLaunchKernelGGL((k_row_steps<NN, WW, II>), grid, dim3(GridSteps<NN>::ROW_NT), 0, st, state, \
                      trans_p, wtrans, soff, twN, bw, groups)
@@ -875,7 +1031,7 @@ int col_tiles(int n) { return (n / 2) / col_tc(n); }
 
 hipError_t launch_col_pass(float2* state, int nwaves, int n, const float2* prop_p,
                            const float2* twN, const float2* tw2, const LaunchTuning& tune,
-                           hipStream_t st) {
+                           hipStream_t st, bool few) {
   if (n == 1024) {
     constexpr int TC = PRISM_COL4_TC32;
     const int tiles = nwaves * (512 / TC);
@@ -889,6 +1045,15 @@ hipError_t launch_col_pass(float2* state, int nwaves, int n, const float2* prop_
     hipLaunchKernelGGL((k_col_pass4<16, 16>),
                        dim3(pass_grid(tiles, 4, tune.col_iters, tune.col_min_wg)), dim3(256), 0, st,
                        state, prop_p, tw2, tiles);
+    return hipGetLastError();
+  }
+  if (few) {
+    const DetBins none{};
+#define COLL(NN)                                                                          \
+  hipLaunchKernelGGL((k_col_lds<NN, false>), dim3((unsigned)(nwaves * col_tiles(NN))),    \
+                     dim3(col_nt(NN)), 0, st, state, prop_p, twN, none, (double*)nullptr)
+    PRISM_DISPATCH_FEW(n, COLL)
+#undef COLL
     return hipGetLastError();
   }
 #define COL(NN)                                                                                 \
@@ -909,8 +1074,9 @@ hipError_t launch_col_detect(const float2* state, int nwaves, int n, const float
                              const float2* twN, const DetBins& bins, double* partial,
                              hipStream_t st) {
 #define COLD(NN)                                                                                 \
-  hipLaunchKernelGGL((k_col_detect<NN>), dim3((unsigned)(nwaves * col_tiles(NN))),               \
-                     dim3(col_nt(NN)), 0, st, state, prop_p, twN, bins, partial)
+  hipLaunchKernelGGL((k_col_lds<NN, true>), dim3((unsigned)(nwaves * col_tiles(NN))),            \
+                     dim3(col_nt(NN)), 0, st, const_cast<float2*>(state), prop_p, twN, bins,    \
+                     partial)
   PRISM_DISPATCH_N(n, COLD)
 #undef COLD
   return hipGetLastError();

@@ -82,13 +82,14 @@ int four_step_radix(int n) { return n == 1024 ? 32 : (n == 256 ? 16 : 0); }
 hipError_t launch_twiddles2(float2*, int, hipStream_t st) { return launch(st); }
 hipError_t launch_row_pass(float2*, int, int, const float2*, const float2*, const float2*,
                            const LaunchTuning&, hipStream_t st, const BeamWaves*,
-                           const float2* const*, size_t) {
+                           const float2* const*, size_t, bool) {
   return launch(st);
 }
 hipError_t launch_col_pass(float2*, int, int, const float2*, const float2*, const float2*,
-                           const LaunchTuning&, hipStream_t st) {
+                           const LaunchTuning&, hipStream_t st, bool) {
   return launch(st);
 }
+bool few_waves(int, int) { return false; }
 hipError_t launch_col_detect(const float2*, int, int, const float2*, const float2*, const DetBins&,
                              double*, hipStream_t st) {
   return launch(st);
