@@ -4,7 +4,9 @@
 // Compiled with plan.cpp by test_build_lanes.py; no GPU and no HIP library.
 //
 // argv: n, slices, f, bytes of workspace beyond the minimum, failing launch
-// (-1: none). Prints "<status> <streams used> <launches> <ordered 0/1>".
+// (-1: none). Prints "<status> <streams used> <launches> <ordered 0/1> <states
+// in bounds and apart 0/1> <planes written once 0/1>".
+#include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -21,6 +23,19 @@ std::map<void*, Clock> g_event;
 long g_launches = 0, g_fail_at = -1;
 char g_handles[64];
 int g_handle = 0;
+
+// device addresses: never read, only compared
+const uintptr_t kWs = uintptr_t(1) << 32, kS = uintptr_t(1) << 44;
+std::map<void*, std::pair<uintptr_t, uintptr_t>> g_state;  // per stream: lowest, highest address
+std::vector<int> g_planes;                                 // times each beam's plane was written
+
+void state_used(const void* p, size_t bytes, void* st) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = a + bytes;
+  auto it = g_state.emplace(st, std::make_pair(a, b)).first;
+  if (a < it->second.first) it->second.first = a;
+  if (b > it->second.second) it->second.second = b;
+}
+size_t wave_bytes(int n) { return (size_t)n * (n / 2) * sizeof(float2); }
 
 void op(void* st) { ++g_stream[st][st]; }
 hipError_t launch(hipStream_t st) {
@@ -80,13 +95,15 @@ hipError_t launch_probe_init(float2*, const double*, int, int, int, const ProbeO
 }
 int four_step_radix(int n) { return n == 1024 ? 32 : (n == 256 ? 16 : 0); }
 hipError_t launch_twiddles2(float2*, int, hipStream_t st) { return launch(st); }
-hipError_t launch_row_pass(float2*, int, int, const float2*, const float2*, const float2*,
-                           const LaunchTuning&, hipStream_t st, const BeamWaves*,
+hipError_t launch_row_pass(float2* state, int nwaves, int n, const float2*, const float2*,
+                           const float2*, const LaunchTuning&, hipStream_t st, const BeamWaves*,
                            const float2* const*, size_t, bool) {
+  state_used(state, nwaves * wave_bytes(n), st);
   return launch(st);
 }
-hipError_t launch_col_pass(float2*, int, int, const float2*, const float2*, const float2*,
-                           const LaunchTuning&, hipStream_t st, bool) {
+hipError_t launch_col_pass(float2* state, int nwaves, int n, const float2*, const float2*,
+                           const float2*, const LaunchTuning&, hipStream_t st, bool) {
+  state_used(state, nwaves * wave_bytes(n), st);
   return launch(st);
 }
 bool few_waves(int, int) { return false; }
@@ -98,7 +115,12 @@ int col_tiles(int n) { return n / 16; }
 hipError_t launch_reduce_partials(const double*, int, int, int, double*, OutAcc, hipStream_t st) {
   return launch(st);
 }
-hipError_t launch_extract(const float2*, int, int, float2*, const float2*, hipStream_t st) {
+hipError_t launch_extract(const float2* state, int nwaves, int n, float2* S, const float2*,
+                          hipStream_t st) {
+  state_used(state, nwaves * wave_bytes(n), st);
+  const size_t first = (reinterpret_cast<uintptr_t>(S) - kS) / (wave_bytes(n) / 2);
+  for (int k = 0; k < nwaves; ++k)
+    if (first + k < g_planes.size()) ++g_planes[first + k];
   return launch(st);
 }
 int contract_tile_slots(int, int, int, int, Prec) { return 1; }
@@ -150,17 +172,29 @@ int main(int argc, char** argv) {
       prism_set_potential_slices(plan, &phase))
     return 4;
   g_fail_at = atol(argv[5]);
-  char device[2];
-  hipStream_t st = reinterpret_cast<hipStream_t>(&device[1]);
+  g_planes.assign(sbytes / (wave_bytes(n) / 2), 0);
+  char caller;
+  hipStream_t st = reinterpret_cast<hipStream_t>(&caller);
   const int status =
-      prism_build_smatrix(plan, f, amax, device, sbytes, device, least + more, st);
+      prism_build_smatrix(plan, f, amax, reinterpret_cast<void*>(kS), sbytes,
+                          reinterpret_cast<void*>(kWs), least + more, st);
   int used = 0, ordered = 1;
   for (auto& s : g_stream) {
     const long count = s.second[s.first];
     used += count > 0;
     if (g_stream[st][s.first] != count) ordered = 0;
   }
-  printf("%d %d %ld %d\n", status, used, g_launches, ordered);
+  int apart = 1, once = 1;
+  uintptr_t end = kWs;
+  std::map<uintptr_t, uintptr_t> ranges;
+  for (auto& r : g_state) ranges.insert(r.second);
+  for (auto& r : ranges) {
+    if (r.first < end) apart = 0;
+    end = r.second;
+  }
+  if (ranges.size() != g_state.size() || end > kWs + least + more) apart = 0;
+  for (int k : g_planes) once = once && k == 1;
+  printf("%d %d %ld %d %d %d\n", status, used, g_launches, ordered, apart, once);
   prism_plan_destroy(plan);
   return 0;
 }

@@ -33,15 +33,26 @@ def lanes(tmp_path_factory):
 # workspaces that hold all 161 beams, 41 and 8 of them (state of one: 1 MiB)
 @pytest.mark.parametrize("more", [1 << 30, 40 << 20, 7 << 20])
 def test_error_between_fork_and_join_still_joins(lanes, more):
-    status, streams, launches, ordered = lanes(512, 12, 4, more, -1)
+    status, streams, launches, ordered, apart, once = lanes(512, 12, 4, more, -1)
+    assert (apart, once) == (1, 1)
     assert (status, streams, ordered) == (0, 2, 1)
     for fail in (launches // 3, launches // 2, launches - 2, launches - 1):
-        status, streams, queued, ordered = lanes(512, 12, 4, more, fail)
+        status, streams, queued, ordered, apart, _ = lanes(512, 12, 4, more, fail)
         assert (status, queued) == (HIP_ERROR, fail + 1)
-        assert ordered == 1, (more, fail)
+        assert (ordered, apart) == (1, 1), (more, fail)
     assert streams == 2
 
 
 def test_small_build_stays_on_the_callers_stream(lanes):
-    status, streams, _, ordered = lanes(128, 2, 4, 1 << 24, -1)
-    assert (status, streams, ordered) == (0, 1, 1)
+    status, streams, _, ordered, apart, once = lanes(128, 2, 4, 1 << 24, -1)
+    assert (status, streams, ordered, apart, once) == (0, 1, 1, 1, 1)
+
+
+# 161, 97, 49 and 5 beams on workspaces for 1 wave up to more than all of them
+@pytest.mark.parametrize("n,H,f", [(512, 4, 4), (768, 12, 8), (1024, 12, 16), (2048, 12, 128)])
+def test_lanes_stay_inside_the_workspace(lanes, n, H, f):
+    wave = 8 * n * (n // 2)
+    for waves in (*range(1, 12), 23, 24, 25, 47, 48, 49, 50, 96, 97, 98, 160, 161, 162, 200):
+        status, streams, _, ordered, apart, once = lanes(n, H, f, (waves - 1) * wave, -1)
+        assert (status, ordered, apart, once) == (0, 1, 1, 1), waves
+        assert streams == (1 if waves == 1 else 2), waves
