@@ -135,6 +135,8 @@ int contract_tile_slots(int w, int window_tile_div, int groups, int group, Prec 
 constexpr int kC16KB = 32;  // 32-bit words per K block row
 __host__ __device__ constexpr int prec_block_beams(Prec p) { return p == Prec::kF32 ? 16 : 32; }
 __host__ __device__ constexpr int prec_words(Prec p) { return p == Prec::kF32 ? 2 : 1; }
+// Rows of a packed coefficient (A) block per probe: FP32 blocks are real-ified.
+__host__ __device__ constexpr int prec_rows(Prec p) { return p == Prec::kF32 ? 2 : 1; }
 // FP16 operands carry a power-of-two scale per beam.
 __host__ __device__ constexpr bool prec_scaled(Prec p) { return p == Prec::kFP16; }
 // scale[a] = 2^-e with e the smallest integer such that every |Re|, |Im| of
@@ -164,7 +166,7 @@ hipError_t launch_alpha16(const double* probe_xy, int p0, int np, const ActiveBe
 constexpr int kMaxSeg = 16;
 struct ContractSeg {
   const uint32_t* s16;  // packed S of its specimen: [ns^2][rowlen] words
-  const uint32_t* a16;  // [groups][K blocks][2G (16-bit: G)][32 words]
+  const uint32_t* a16;  // [groups][K blocks][prec_rows G][32 words]
   const int2* origin;   // [np] window origins
   float2* window;       // [np][w][w]
   int rowlen;           // 32-bit words per packed pixel row

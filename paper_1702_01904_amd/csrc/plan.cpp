@@ -440,7 +440,7 @@ struct ProbeBatchWs {
   std::vector<PackWs> packs;
   std::vector<uint16_t*> pix;  // per pixel-list set: bins as lists of window pixels
   std::vector<prism::BinLists*> lists;
-  uint32_t* a16;    // packed alpha: [groups][K blocks][2G (16-bit: G)][32 words]
+  uint32_t* a16;    // packed alpha: [groups][K blocks][prec_rows G][32 words]
   int2* origin;     // [chunk]
   float2* window;   // [chunk][w][w]
   double* partial;  // W > 128: [chunk][tiles][PRISM_MAX_DET] detector partials
@@ -473,7 +473,7 @@ size_t probe_batch_layout(int w, int G, prism::Prec pk, const std::vector<PackSh
   // a chunk's pieces (at most one per request, kMaxSeg at most) each add
   // at most one partial group to the chunk / G whole ones
   const int groups = chunk / G + std::min(prism::kMaxSeg, std::max(n_reqs, 1)) - 1;
-  bw->a16 = c.take<uint32_t>((size_t)groups * nblk_max * 2 * G * prism::kC16KB);
+  bw->a16 = c.take<uint32_t>((size_t)groups * nblk_max * prism::prec_rows(pk) * G * prism::kC16KB);
   bw->origin = c.take<int2>(chunk);
   bw->window = c.take<float2>((size_t)chunk * w * w);
   bw->partial = prism::window_big(w)
@@ -746,7 +746,7 @@ int run_sub(std::vector<Req>& rq, const Sub& sb, int chunk, void* base, hipStrea
       cs.s[k] = prism::ContractSeg{pw.s16, a16, bw.origin + x.begin, bw.window + x.begin * w2,
                                    r.n_actp * prism::prec_words(pr), r.ns, x.np, g, r.out_scale};
       g += ngrp;
-      a16_off += (size_t)ngrp * nblk * 2 * G * prism::kC16KB;
+      a16_off += (size_t)ngrp * nblk * prism::prec_rows(pr) * G * prism::kC16KB;
     }
     cs.groups = g;
     if (!packed)

@@ -378,7 +378,7 @@ template <int G>
 __device__ __forceinline__ void contract32(const GroupWork& wk, const int* rylo, const int* ryhi,
                                            uint32_t* buf0, uint32_t* buf1) {
   constexpr int RT = G / 8;
-  constexpr int AROWS = 2 * G;
+  constexpr int AROWS = prec_rows(Prec::kF32) * G;
   static_assert(AROWS * 8 % kNT16 == 0 && kTile16 * 8 % kNT16 == 0,
                 "every thread stages whole 16-byte segments of A and B");
   constexpr int NAQ = AROWS * 8 / kNT16;     // u32x4 of the A block per thread
@@ -660,7 +660,7 @@ __attribute__((amdgpu_waves_per_eu(P == Prec::kF32 ? 2 : 3))) void k_contract16(
     const ContractSegs segs, int w, int slots, int set) {
   // two arrays, one per buffer (A block, then B block)
   constexpr bool F32 = P == Prec::kF32;
-  constexpr int LDSB = ((F32 ? 2 : 1) * G + kTile16) * kC16KB;
+  constexpr int LDSB = (prec_rows(P) * G + kTile16) * kC16KB;
   __shared__ uint32_t sbuf0[LDSB], sbuf1[LDSB];
   __shared__ int offx[G], offy[G];
   __shared__ int zero[G];
@@ -688,7 +688,7 @@ __attribute__((amdgpu_waves_per_eu(P == Prec::kF32 ? 2 : 3))) void k_contract16(
   const int p_base = grp * G;
   const int gcount = min(G, np - p_base);
   const int nblk = rowlen / kC16KB;
-  const uint32_t* a16g = sg.a16 + (size_t)grp * nblk * ((F32 ? 2 : 1) * G) * kC16KB;
+  const uint32_t* a16g = sg.a16 + (size_t)grp * nblk * (prec_rows(P) * G) * kC16KB;
   if (tid < 64) {
     // group geometry in wave 0, one lane per probe (G <= 64): offsets of
     // each window from the first, their extent, and the union origin
