@@ -1255,14 +1255,20 @@ int prism_build_smatrix(prism_plan* p, int f, double amax_mrad, void* S, size_t 
   // group's VALU-bound row pass overlaps the other's memory-bound column pass
   // (n = 1024, 373 beams, 12 slices: 15.8 ms against 17.0 on one stream; n =
   // 2048, 101 beams, 6 slices: 11.4 against 12.1). Forking and joining the
-  // streams costs about 80 us, so builds whose passes move less than 1 GiB
-  // (0.2 ms of HBM) keep one: n = 128, 49 beams, 4 slices (51 MB) take 63 us
-  // on one stream and 140 on two, n = 256, 161 beams, 8 slices (1.3 GB) 370
-  // and 333. Per-kernel timing (prism_profile_enable) also keeps one lane, so
-  // that no time includes a co-running kernel.
-  const double moved = 4.0 * B * p->H * (double)state_bytes(n);
+  // streams costs about 20 us, and twice the launches need passes that are longer
+  // than a launch: builds whose passes move less than 1 GiB in all (0.2 ms of
+  // HBM) or 20 MiB per slice keep one lane. One lane / two, us: n = 512, 21
+  // beams, 2, 8 and 20 slices (0.16, 0.66, 1.6 GiB) 97 / 108, 317 / 307, 753 /
+  // 705; n = 384, 97 beams, 2, 5 and 10 slices (0.4, 1.1, 2.1 GiB) 158 / 171, 345
+  // / 352, 655 / 657; n = 1152, 21 beams, 1, 3 and 8 slices (0.4, 1.2, 3.3 GiB)
+  // 188 / 193, 479 / 459, 1209 / 1133; per slice: n = 128, 49 beams, 200 slices
+  // (12 MiB each) 2258 / 3042; n = 256, 21 beams, 60 slices (21 MiB) 991 / 967; n =
+  // 256, 49 beams, 40 slices (49 MiB) 1098 / 903. Per-kernel timing
+  // (prism_profile_enable) also keeps one lane, so that no time includes a
+  // co-running kernel.
+  const double per_slice = 4.0 * B * (double)state_bytes(n);
   const int lanes = (PRISM_BUILD_STREAMS > 1 && !p->prof_on && chunk >= 2 && B >= 2 &&
-                     moved >= (double)(1 << 30)) ? 2 : 1;
+                     per_slice * p->H >= (double)(1 << 30) && per_slice >= 20.0 * (1 << 20)) ? 2 : 1;
   // one chunk: its two halves (the state holds B waves); two: half a chunk each
   const int sub = lanes == 1 ? chunk : (B <= chunk ? (B + 1) / 2 : chunk / 2);
   hipStream_t ls[2] = {st, st};

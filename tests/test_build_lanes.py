@@ -43,8 +43,10 @@ def test_error_between_fork_and_join_still_joins(lanes, more):
     assert streams == 2
 
 
-def test_small_build_stays_on_the_callers_stream(lanes):
-    status, streams, _, ordered, apart, once = lanes(128, 2, 4, 1 << 24, -1)
+# little in all; much in all, but in passes shorter than a launch
+@pytest.mark.parametrize("n,H,f", [(128, 2, 4), (128, 300, 2)])
+def test_small_passes_stay_on_the_callers_stream(lanes, n, H, f):
+    status, streams, _, ordered, apart, once = lanes(n, H, f, 1 << 24, -1)
     assert (status, streams, ordered, apart, once) == (0, 1, 1, 1, 1)
 
 
