@@ -323,7 +323,9 @@ int prism_probe_batch(const prism_probe_request* requests, int count, void* ws,
  * iFFT[A e^{-i chi} e^{-2 pi i q.r0}] n / sqrt(N_A) (tilt as in prism_optics),
  * H slice steps,
  * I = |FFT psi_H|^2 / n^2 integrated per detector bin: out_dev float64
- * [P][n_det]. */
+ * [P][n_det]. Results do not depend on the workspace; calls of few probes (the
+ * line is between 1 and 64 of them, by n) may differ from longer ones in the
+ * rounding of the transforms (about 1e-6 relative). */
 int prism_multislice_outputs(prism_plan* plan, const double* probe_xy_dev, int n_probes,
                              const prism_optics* optics, const prism_detector* detector,
                              double* out_dev, void* ws, size_t ws_bytes, void* stream);
@@ -486,14 +488,15 @@ int prism_server_call_stats(const prism_server* server, long long* probe_calls,
 
 /* Launch shapes of a plan, none of which changes any result (the same
  * operations run in the same order; only their distribution over
- * workgroups and launches changes), chosen per grid by a tuning sweep on
- * the target GPU. A zero field means the library default (shown).
+ * workgroups and launches changes), chosen per grid by measurement on the
+ * target GPU. A zero field means the library default (shown).
  *   row_iters, col_iters: most row groups / column tiles one workgroup of
  *     the slice passes walks (powers of two up to 64; 16, 8);
  *   row_min_groups, col_min_groups: fewest workgroups a slice-pass launch
  *     has where there is that much work (512, 256);
  *   wave_chunk_mib: wave state per slice-pass launch, which sets the
- *     preferred build and multislice workspaces (16 .. 65536; 256);
+ *     preferred build and multislice workspaces (16 .. 65536; 256; 192 keeps
+ *     it in the Infinity Cache between passes, which pays in most builds);
  *   probe_group: probes per window-sum group (16, 32, 64; 0: with FP32
  *     operands 64 for W >= 128, 32 for W >= 64, else 16; with 16-bit operands
  *     64 for W >= 48, else 16, and smaller groups down to 16 on a workspace

@@ -65,7 +65,7 @@ _TUNING = None
 
 
 def _tuning_table():
-    """Per-grid launch shapes from the committed sweep (tuning_gfx950.json), or {}."""
+    """Per-grid launch shapes from the committed table (tuning_gfx950.json), or {}."""
     global _TUNING
     if _TUNING is None:
         import json

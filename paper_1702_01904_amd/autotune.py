@@ -13,8 +13,15 @@ shapes, one parameter at a time (each starting from the best found so far):
 
 A candidate is kept only if its S-matrix and probe outputs equal the default
 shapes' bit for bit (none of these shapes may change a result). The winners
-go to tuning_gfx950.json beside this file, which Plan applies when it is
-created for that n.
+go to --out. Differences of a few per cent between two sweeps are noise, so a
+winner is compared over whole builds before it enters tuning_gfx950.json
+beside this file, which Plan applies when it is created for that n. In the
+committed table wave_chunk_mib comes from such a comparison (192 MiB on every
+grid but 128^2: at n = 1024 a sweep prefers 128, which takes 16.8 ms where 192
+takes 16.2; builds whose whole state is 192 to 256 MiB would be up to 10 %
+faster in one chunk of 256, larger ones up to 14 % slower), row_* and col_* are winners of a sweep of earlier slice passes
+that still hold, and the probe fields are the library's defaults. build_ms and
+probe_ms are [defaults, committed shapes] of the present kernels.
 
 Usage (on the GPU): python -m paper_1702_01904_amd.autotune [--out PATH] [--n 256,1024]
 """

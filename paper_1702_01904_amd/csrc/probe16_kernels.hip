@@ -24,11 +24,11 @@
 //    steps; K' is visited as 4 (l/16) + 16 ks + s on both operands, a
 //    permutation of the block's 32 real K' indices, so the sum is the same.
 //    The scale is 1.
-//  * Staging: 16-bit K blocks pass through registers into padded LDS rows,
-//    two blocks ahead (these sums are bound by operand fetch); FP32 K blocks go
-//    straight from global memory into XOR-swizzled LDS rows
-//    (global_load_lds_dwordx4), one block ahead, which frees the staging
-//    registers for reading both K steps' operands before their products.
+//  * Staging: K blocks go straight from global memory into XOR-swizzled LDS rows
+//    (global_load_lds_dwordx4), one block ahead of the products, in both forms.
+//    FP32 waves read both K steps' operands of a block before its products;
+//    16-bit ones load the first block of the workgroup's next tile during the
+//    last products of this one.
 //  * The 1 / (W sqrt(B_A)) normalisation is applied in FP32 at the end.
 #include <algorithm>
 
@@ -299,7 +299,6 @@ struct C16 {
 };
 constexpr int kCT32 = 2;
 constexpr int kTile16 = 128;  // union pixels per workgroup
-constexpr int kPitch16 = 36;             // uint32 per LDS row (32 + 4 pad)
 
 // What a workgroup sums: a list of items, each one union tile of 128 pixels
 // for the whole group, or (mode 1) one tile of one probe's own window.
@@ -522,8 +521,8 @@ __device__ __forceinline__ void contract32(const GroupWork& wk, const int* rylo,
 // 16-bit sums of the workgroup's items. Probe tile r of a wave: the operand
 // read holds (Re, -Im) of 16 probes; swapping the halves of each word and
 // flipping the low one's sign gives (Im, Re), so the wave's two products are
-// the real and the imaginary parts of the sums. The next item's first two K
-// blocks are fetched during the last products of this one. Bound: the L2 /
+// the real and the imaginary parts of the sums. The next item's first K block
+// is fetched during the last products of this one. Bound: the L2 /
 // Infinity Cache traffic and latency of the pixel rows.
 template <int G, Prec P>
 __device__ __forceinline__ void contract16(const GroupWork& wk, uint32_t* buf0, uint32_t* buf1) {
@@ -652,8 +651,12 @@ __device__ __forceinline__ void contract16(const GroupWork& wk, uint32_t* buf0, 
   }
 }
 
-// Grid: x walks the union tiles of a group, y the probe groups of every
-// segment (segment k owns groups g_begin .. g_begin + ceil(np / G)).
+// Grid: one dimension of (group, slot) pairs over the probe groups of every
+// segment (segment k owns groups g_begin .. g_begin + ceil(np / G)); the slots of
+// a group share its union tiles round-robin. set == 0: slots of a group adjacent.
+// set > 0: `set` neighbouring groups and all their slots run on one XCD
+// (workgroups are dealt to the 8 XCDs by blockIdx % 8), one group of the set
+// after the other at the same slot, so that its L2 serves the pixels they share.
 template <int G, Prec P>
 __global__ __launch_bounds__(kNT16)
 __attribute__((amdgpu_waves_per_eu(P == Prec::kF32 ? 2 : 3))) void k_contract16(

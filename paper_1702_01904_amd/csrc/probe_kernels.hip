@@ -635,8 +635,11 @@ inline unsigned blocks_for(size_t n, unsigned bs) { return (unsigned)((n + bs - 
 // 64 as soon as a window is three tiles wide. Measured (window sum, groups of
 // 16 / 32 / 64, 12800 raster probes): FP32 W = 64 722 / 660 / 770 us, W = 96
 // 2767 / 2628 / 2943 us, W = 144 13.8 / 13.1 / 11.8 ms; BF16 W = 48 94 / 85 /
-// 78 us, W = 64 205 / 176 / 156 us, W = 128 2569 / 1666 / 1236 us; 1280 probes
-// at W = 24: FP32 16 / 17 / 22, BF16 11 / 11 / 15 us.
+// 78 us, W = 64 205 / 176 / 156 us, W = 128 2569 / 1666 / 1236 us. Below W = 48
+// that many probes would do a little better in larger groups (FP32 W = 32 83 / 79
+// / 98, BF16 W = 32 39 / 35 / 33, W = 16 24 / 21 / 22 us), fewer or scattered
+// ones worse (1200 scattered probes, FP32 W = 16 17 / 26 / 47, BF16 W = 32 24 /
+// 28 / 39 us on 768^2; 30 probes, FP32 W = 32 9 / 12 / 13 us): 16 for them all.
 int contract_group(int w, Prec pr) {
   if (pr != Prec::kF32) return w >= 48 ? 64 : 16;
   return w >= 128 ? kCG128 : (w >= 64 ? 32 : 16);

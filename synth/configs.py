@@ -44,7 +44,7 @@ CONFIGS = {
         detectors=[(0.0, 20.0), (20.0, 40.0), (40.0, 80.0), (80.0, 150.0)],
         f_values=(1, 2, 4),
     ),
-    # 512^2 case (the radix-8/2 Stockham slice kernels, windows of 128 and
+    # 512^2 case (the two-step register-DFT slice kernels, windows of 128 and
     # 64 at f = 2 and 4); sampled against one-probe oracle runs.
     "s512": dict(
         specimen=dict(kind="random", cell=(51.2, 51.2, 12.0), n_atoms=400,
