@@ -298,9 +298,17 @@ __host__ __device__ constexpr bool bit_fields() {
 // The window transforms' arithmetic with every multiply-add written out, so
 // that their results do not depend on what the compiler contracts in the code
 // around it: a b, and the 8- and 3-point DFTs of fft_lds.hpp (2 and 4 points
-// have no products). One form for every stage, window side and butterfly.
-__device__ __forceinline__ float2 cmul_fma(float2 a, float2 b) {
-  return make_float2(__builtin_fmaf(a.x, b.x, -(a.y * b.y)), __builtin_fmaf(a.x, b.y, a.y * b.x));
+// have no products). xb says which of the imaginary part's two products is
+// rounded on its own. Neither form is the more exact one (FP32, W = 128, against
+// 64 bits: 2.4e-7 with the choice below, 2.2e-7 with one form throughout). The
+// choice per butterfly (WinFft) follows what the compiler once contracted, so
+// that the FP64 detector sums repeat earlier versions' to 1e-15 (W <= 72: the
+// same additions; above, squares of real and imaginary parts are added apart);
+// one form throughout moves them by 2e-8.
+__device__ __forceinline__ float2 cmul_fma(float2 a, float2 b, bool xb) {
+  const float fx = xb ? a.x : a.y, fy = xb ? b.y : b.x;  // the fused pair
+  const float rx = xb ? a.y : a.x, ry = xb ? b.x : b.y;  // the rounded one
+  return make_float2(__builtin_fmaf(a.x, b.x, -(a.y * b.y)), __builtin_fmaf(fx, fy, rx * ry));
 }
 // z + s (x, y)
 __device__ __forceinline__ float2 madd(float2 z, float s, float x, float y) {
@@ -340,26 +348,27 @@ __device__ __forceinline__ void dft_fma(float2 (&v)[R]) {
 // Inputs of one butterfly times w^r, w = exp(-2 pi i k / (NS R)): w, w^2, w^4
 // from the table, the other powers as products (as stage_in).
 template <class B, int R, int NS>
-__device__ __forceinline__ void stage_twiddle(const float2* tw, int k, float2 (&v)[R]) {
+__device__ __forceinline__ void stage_twiddle(const float2* tw, int k, bool xb, float2 (&v)[R]) {
   constexpr int TWS = B::L / (NS * R);
   float2 w[R];
   if constexpr (R == 2 || R == 4 || R == 8) {
     w[1] = tw[k * TWS];
     if constexpr (R >= 4) w[2] = tw[2 * k * TWS];
-    if constexpr (R == 4) w[3] = cmul_fma(w[1], w[2]);
+    if constexpr (R == 4) w[3] = cmul_fma(w[1], w[2], false);
     if constexpr (R == 8) {
       w[4] = tw[4 * k * TWS];
-      w[3] = cmul_fma(w[1], w[2]);
-      w[5] = cmul_fma(w[1], w[4]);
-      w[6] = cmul_fma(w[2], w[4]);
-      w[7] = cmul_fma(w[3], w[4]);
+      w[3] = cmul_fma(w[1], w[2], false);
+      w[5] = cmul_fma(w[1], w[4], false);
+      w[6] = cmul_fma(w[2], w[4], false);
+      w[7] = cmul_fma(w[3], w[4], false);
     }
   } else {
 #pragma unroll
     for (int r = 1; r < R; ++r) w[r] = tw[r * k * TWS];
   }
 #pragma unroll
-  for (int r = 1; r < R; ++r) v[r] = cmul_fma(v[r], w[r]);
+  for (int r = 1; r < R; ++r)
+    v[r] = cmul_fma(v[r], w[r], xb && !(B::L == 128 && r == 4));
 }
 
 // Part PT of a stage's outputs to LDS / of its inputs from LDS (element
@@ -422,6 +431,15 @@ struct WinFft {
   using Rows = RowBatch<W, W>;
   using Cols = Batch<W, W, W, 0, 1, W, true>;
 
+  // xb of a stage's butterflies past the first NT: set where the stage's
+  // twiddles repeat every NT butterflies.
+  template <class B, int R, int NS>
+  __device__ __forceinline__ static constexpr bool round_xb() {
+    constexpr int NB = B::L / R;
+    return B::SEQ_FAST ? (W & (W - 1)) == 0 && (NT / W) % NS == 0
+                       : (NB & (NB - 1)) == 0 && NT % NB == 0;
+  }
+
   // From the inputs v of the stage (B, NS) (twiddles applied) through the
   // rest of the 2D transform; fin(v) gets the outputs of the last column
   // stage (radix next_radix(W / span), see last_span).
@@ -470,7 +488,7 @@ struct WinFft {
         if (SI::GUARD && b >= SI::TOT) continue;
         int s, j;
         stage_coords<BI, SI::NB>(b, s, j);
-        stage_twiddle<BI, RI, NSI>(tw, j % NSI, u[p]);
+        stage_twiddle<BI, RI, NSI>(tw, j % NSI, p > 0 && round_xb<BI, RI, NSI>(), u[p]);
         // one butterfly's twiddles at a time: no registers for all of them
         if constexpr (SI::PER * RI >= 24) __builtin_amdgcn_sched_barrier(0);
       }
