@@ -40,9 +40,9 @@ CONFIG = "fcc1024"
 # write x1.0), as in the HBM-traffic summary under profiles/. Valid only for
 # the kernel sources with this hash (of their code, comments aside); reported
 # as null otherwise.
-TRAFFIC_SRC_SHA = "175adbe2521e172b"
-TRAFFIC_BYTES = {"row_pass": 426327492, "col_pass": 391434107, "contract": 4440993601,
-                 "s32_pack": 1310761703, "window_detect": 1141250572, "contract16": 2355982813,
+TRAFFIC_SRC_SHA = "66dab1040a92ca5e"
+TRAFFIC_BYTES = {"row_pass": 426574465, "col_pass": 391434107, "contract": 4456378039,
+                 "s32_pack": 1310763137, "window_detect": 1140925180, "contract16": 2351962465,
                  "s16_pack": 975254243}
 
 

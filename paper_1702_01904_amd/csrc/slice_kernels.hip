@@ -390,13 +390,13 @@ __global__ __launch_bounds__(TC * R) __attribute__((amdgpu_waves_per_eu(2))) voi
 // Twiddles stay in registers for the whole kernel; a workgroup walks row
 // groups (gridDim.x apart) with the next group's inputs and the current
 // group's t_p in flight during the transforms.
-// Bound: VALU issue (n = 1536: 68 VALU instructions per row element, issue
-// near 100 % busy at two waves per SIMD while the state stays in the Infinity
-// Cache). R1 values per lane keep the exchanges at two per transform, against
-// three LDS round trips and a workgroup barrier pair each for the radix-8 LDS
-// stages this replaces: 99 instead of 209 us per 20- and 27-wave launch at n =
-// 1536 (3.8 against 2.6 TB/s), 123 instead of 208 us for 11 and 14 waves at n
-// = 2048.
+// Bound: VALU issue and memory together (n = 1536: 64 VALU instructions per row
+// element, issue 70 % busy at 5.4 TB/s in a launch of 10 waves alone; n = 2048:
+// 56 % at 5.8 TB/s, half of it t_p). R1 values per lane keep the exchanges at
+// two per transform, against three LDS round trips and a workgroup barrier pair
+// each for the radix-8 LDS stages this replaces: 99 instead of 209 us per 20-
+// and 27-wave launch at n = 1536 (3.8 against 2.6 TB/s), 123 instead of 208 us
+// for 11 and 14 waves at n = 2048.
 // WT and INIT as in the four-step pass.
 template <int N, bool WT, bool INIT>
 __global__ __launch_bounds__(GridSteps<N>::ROW_NT) __attribute__((amdgpu_waves_per_eu(2)))
@@ -478,7 +478,8 @@ void k_row_steps(float2* __restrict__ state, const float2* __restrict__ trans,
 // XCD-grouped as in the four-step pass) with the next tile in flight.
 // Bound: the workgroup's phases (loads, VALU, LDS exchanges) overlap only
 // through the prefetch, since one workgroup fills a compute unit's registers
-// (n = 1536: VALU 49 % busy, 3.6 TB/s); 102 instead of 174 us per 20- and
+// (n = 1536: VALU issue 32 % busy, 3.4 TB/s, waves waiting for loads or at
+// barriers 30 % of their cycles); 102 instead of 174 us per 20- and
 // 27-wave launch at n = 1536, 101 instead of 155 us for 11 and 14 waves at n =
 // 2048, against the radix-8 LDS stages this replaces.
 template <int N>
